@@ -206,6 +206,16 @@ __device__ __forceinline__ T* field_ptr(T* U, int f, size_t fs) {
   return U + field_off(f, fs);
 }
 
+// The same for the kernels that loop over bricks: the field size itself (in bytes, below 2^32) is
+// made opaque, so that the 25 products f * size do not stay live from brick to brick either; each use
+// costs two scalar multiplies.
+template <class T>
+__device__ __forceinline__ T* field_at(T* U, int f, size_t fs) {
+  uint32_t b = (uint32_t)(fs * 8);
+  asm volatile("" : "+s"(b));
+  return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(U) + (uint64_t)f * b);
+}
+
 // A per-phase copy of the neighbour offsets that the compiler cannot prove equal
 // to the other phases' copies, so the address arithmetic is redone per field
 // instead of being kept live across the whole point evaluation.
@@ -448,13 +458,9 @@ __device__ __forceinline__ void flux_divergence(const double* F, size_t fs, int 
   }
 }
 
-// Conformal Christoffels from d gt: Gt_kij = 1/2 (d_i gt_kj + d_j gt_ki - d_k gt_ij)
-// (first index lowered, local), Gu[k][ij] = Gt^k_ij, Gd^k = gt^ij Gt^k_ij; and
-// adds to Ric the terms quadratic in the connection:
-//   1/2 Gd^k (Gt_ijk + Gt_jik) + gt^lm (Gt^k_li Gt_jkm + Gt^k_lj Gt_ikm + Gt^k_im Gt_klj)
-__device__ __forceinline__ void connection_and_quadratic_ricci(const double dgt[6][3], const double gi[6],
-                                                               double Gu[3][6], double Gd[3], double Ric[6]) {
-  double Gl[3][6];
+// Conformal Christoffels from d gt, first index lowered (local):
+// Gl[k][ij] = Gt_kij = 1/2 (d_i gt_kj + d_j gt_ki - d_k gt_ij).
+__device__ __forceinline__ void connection_lower(const double dgt[6][3], double Gl[3][6]) {
 #pragma unroll
   for (int k = 0; k < 3; ++k)
 #pragma unroll
@@ -462,12 +468,23 @@ __device__ __forceinline__ void connection_and_quadratic_ricci(const double dgt[
       const int i = SI(s), j = SJ(s);
       Gl[k][s] = 0.5 * ((dgt[S(k, j)][i] + dgt[S(k, i)][j]) - dgt[s][k]);
     }
+}
+
+// Gu[k][ij] = Gt^k_ij and Gd^k = gt^ij Gt^k_ij.
+__device__ __forceinline__ void connection_raise(const double Gl[3][6], const double gi[6], double Gu[3][6],
+                                                 double Gd[3]) {
 #pragma unroll
   for (int k = 0; k < 3; ++k)
 #pragma unroll
     for (int s = 0; s < 6; ++s) Gu[k][s] = gi[S(k, 0)] * Gl[0][s] + gi[S(k, 1)] * Gl[1][s] + gi[S(k, 2)] * Gl[2][s];
 #pragma unroll
   for (int k = 0; k < 3; ++k) Gd[k] = contract_sym(gi, Gu[k]);
+}
+
+// Adds to Ric the terms quadratic in the connection:
+//   1/2 Gd^k (Gt_ijk + Gt_jik) + gt^lm (Gt^k_li Gt_jkm + Gt^k_lj Gt_ikm + Gt^k_im Gt_klj)
+__device__ __forceinline__ void ricci_quadratic(const double Gl[3][6], const double gi[6], const double Gu[3][6],
+                                                const double Gd[3], double Ric[6]) {
   // With Q[j][k][l] = gt^lm Gt_jkm (last index raised; 27 values), every gt^lm
   // contraction of the quadratic terms becomes a single sum over k, l:
   //   gt^lm Gt^k_li Gt_jkm = Gt^k_li Q[j][k][l],  gt^lm Gt^k_im Gt_klj = Gt^k_im Q[k][j][m].
@@ -492,6 +509,14 @@ __device__ __forceinline__ void connection_and_quadratic_ricci(const double dgt[
         r += (Gu[k][S(l, i)] * Q[j][k][l] + Gu[k][S(l, j)] * Q[i][k][l]) + Gu[k][S(i, l)] * Q[k][j][l];
     Ric[s] += r;
   }
+}
+
+__device__ __forceinline__ void connection_and_quadratic_ricci(const double dgt[6][3], const double gi[6],
+                                                               double Gu[3][6], double Gd[3], double Ric[6]) {
+  double Gl[3][6];
+  connection_lower(dgt, Gl);
+  connection_raise(Gl, gi, Gu, Gd);
+  ricci_quadratic(Gl, gi, Gu, Gd, Ric);
 }
 
 // Conformal-factor part of the Ricci tensor added to Ric:

@@ -1,60 +1,34 @@
-// LDS-staged stage kernel: one 256-thread workgroup owns a BX x BY x BZ brick
-// (one point per thread). The 25 fields are visited in a fixed order; for each
-// field the workgroup copies the brick plus its periodic halo of width 3 (the
-// ghost-zone fill, done as an index wrap while loading) from HBM into an LDS
-// buffer with ~NH/256 independent coalesced loads per thread, and every thread
-// then forms that field's derivatives at its point from LDS with
-// compile-time-offset reads. The copy of the next field is issued before the
-// current field's arithmetic and written to the second LDS buffer after it, so
-// its latency hides behind the FP64 work. A workgroup walks several bricks and
-// loads the next brick's first fields, epilogue operands and point values during
-// the last phases of the current one. Long-lived per-point intermediates
-// (R3_* slots) stay in registers: one wave per SIMD is resident anyway (the
-// fused point evaluation needs ~300 registers), so the VGPR + AGPR file holds
-// them, and LDS only carries the two halo buffers. The fluid fluxes come from a
-// pointwise pre-pass (fluid_flux_point) and are differentiated from global loads.
+// LDS-staged stage kernel: a 512-thread workgroup owns a BX x BY x BZ brick of 256 points with two
+// threads per point in two roles, one wave of each role on every SIMD:
+//   curvature waves (0-3)  stage the halo boxes, and form from them the second derivatives, the
+//       connection, the Ricci tensor, D_iD_j alpha and the Gt^i source: everything that ends in
+//       X_ij = -D_iD_j alpha + alpha (R_ij - 8 pi S_ij), its trace-free part, and Gt^i;
+//   transport waves (4-7)  form shift advection and dissipation of every field, the fluid and
+//       the remaining algebra, and run the RK4 epilogue.
+// The whole point evaluation in one thread needs about 470 registers, so one wave per SIMD, whose
+// dependent FP64 operations and LDS reads nothing covers: a lone brick of a 16^3 grid, all data in
+// cache, took 25 us, nearly the 31 us per brick of a full 256^3 grid. Split by role, each half fits
+// 256 registers and the SIMD issues from one wave while the other waits; what the halves owe each
+// other is 8 values one way (inverse metric, pressure, 1 / X) and 10 the other, exchanged in LDS.
 //
-// The arithmetic is that of bssn_rhs_stream in bssn_device.hpp (same
-// operations in the same order); only where the operands come from differs, so
-// the two variants agree to rounding.
+// The 25 fields are visited two per barrier interval in a fixed order (kPairOrder), chosen so that
+// the two roles have about equal work in each: the connection algebra runs while the transport
+// waves advect At_ij, and X_ij is handed over before the last fields. A field's halo box (brick
+// plus width 3, the ghost-zone fill done as an index wrap in the load offsets) goes straight from
+// HBM into a ring of three interval slots by LDS-direct loads, two intervals ahead. The curvature
+// waves issue no other memory operations in steady state, so a count of their newer loads tells
+// when a field has landed; the transport waves' epilogue operands, flux neighbours and stores
+// have their own counters and never delay the ring. A workgroup walks several bricks; the next
+// brick's first fields, point values and recovery are done during the current one's last intervals.
+// The fluid fluxes come from the previous stage (or a pointwise pre-pass) and are differentiated
+// from global loads.
+//
+// The arithmetic is that of bssn_rhs_stream in bssn_device.hpp; only where operands come from, and
+// the order of a few sums, differs, so the two variants agree to rounding.
 #pragma once
-#include <type_traits>
-
 #include "bssn_device.hpp"
 
 namespace cosmos {
-
-enum : int {
-  R3_GI = 0,     // 6  gt^ij
-  R3_E = 6,      // 1  E
-  R3_S = 7,      // 3  S_i
-  R3_P = 10,     // 1  P
-  R3_IX = 11,    // 1  1 / X
-  R3_DB = 12,    // 9  d_a beta^i at 3 i + a
-  R3_RG = 21,    // 3  accumulated Gt^i right-hand side
-  R3_RX = 24,    // 6  R_ij, then X_ij = -D_iD_j alpha + alpha (R_ij - 8 pi S_ij)
-  R3_SG = 30,    // 3  S^jk d_i gt_jk
-  R3_GU = 33,    // 18 d_a gt_ij at 3 ij + a, then Gt^k_ij at 6 k + ij
-  R3_DCHI = 51,  // 3
-  R3_DAL = 54,   // 3
-  R3_D2A = 57,   // 1
-  R3_COUNT = 58
-};
-
-template <int BX, int BY, int BZ>
-struct Brick {
-  static constexpr int X = BX, Y = BY, Z = BZ;   // brick (one point per thread)
-  static constexpr int XO = 3;                  // x offset of the brick in its halo box
-  static constexpr int HX = BX + 6, HY = BY + 6, HZ = BZ + 6;
-  static constexpr int NH = HX * HY * HZ;       // halo-box points
-  static constexpr int NQ = (NH + 255) / 256;   // loads per thread per field
-  static constexpr int NP = NQ * 256;            // padded LDS buffer: every thread copies NQ points
-  static constexpr int SY = HX, SZ = HX * HY;   // LDS strides
-  static constexpr int NOFF = NQ;                // per-thread halo offsets
-  static constexpr int LDS_DOUBLES = 2 * NP;       // two halo buffers
-  static_assert(BX * BY * BZ == 256, "one point per thread");
-  static_assert(LDS_DOUBLES * 8 <= 160 * 1024, "LDS budget");
-};
 
 // Workgroup barrier for LDS staging. __syncthreads() carries a workgroup-scope release fence,
 // which waits for every outstanding global load and store of the wave (s_waitcnt vmcnt(0)) and so
@@ -122,91 +96,12 @@ __device__ __forceinline__ void lds_derivs(const double* c, const DevParams& P, 
   }
 }
 
-// Order in which the fields are staged (one per phase).
-constexpr int kStageOrder[NF] = {F_BET,    F_BET + 1, F_BET + 2, F_GT,     F_GT + 1, F_GT + 2, F_GT + 3,
-                                 F_GT + 4, F_GT + 5,  F_GAM,     F_GAM + 1, F_GAM + 2, F_CHI,   F_ALP,
-                                 F_K,      F_AT,      F_AT + 1,  F_AT + 2, F_AT + 3, F_AT + 4, F_AT + 5,
-                                 F_ET,     F_ST,      F_ST + 1,  F_ST + 2};
-// Phases whose field is differentiated twice (second and mixed derivatives: the shift, the
-// conformal metric, chi and the lapse); the others take first derivatives only.
-constexpr bool kSecondDerivs[NF] = {true,  true,  true,  true,  true,  true,  true,  true,  true,
-                                    false, false, false, true,  true,  false, false, false, false,
-                                    false, false, false, false, false, false, false};
-constexpr int kPrefetch = 2;  // fields in flight ahead of the one being processed
-
-// Fields whose right-hand side becomes final in each phase, in the order they are
-// handed to the sink (the Gt^i right-hand sides complete in the trace-K phase).
-constexpr int kPutCount[NF] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 0, 0, 0, 1, 1, 4, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1};
-constexpr int kPutField[NF][4] = {
-    {F_BET}, {F_BET + 1}, {F_BET + 2}, {F_GT}, {F_GT + 1}, {F_GT + 2}, {F_GT + 3}, {F_GT + 4}, {F_GT + 5},
-    {}, {}, {}, {F_CHI}, {F_ALP}, {F_K, F_GAM, F_GAM + 1, F_GAM + 2},
-    {F_AT}, {F_AT + 1}, {F_AT + 2}, {F_AT + 3}, {F_AT + 4}, {F_AT + 5}, {F_ET}, {F_ST}, {F_ST + 1}, {F_ST + 2}};
-// The RK4 epilogue operands of phase p's outputs (u_n and/or acc at the point) are
-// loaded kEpiAhead phases earlier: they come from HBM, whose latency exceeds one phase.
-constexpr int kEpiAhead = 3;
-
 __device__ __forceinline__ int wrap_halo(int x, int n) {
   x = x < 0 ? x + n : x;
   x = x >= n ? x - n : x;
   return x >= n ? x - n : x;
 }
 
-// Cooperative copy of the fields' halo boxes: a ring of kPrefetch register
-// sets (slot 0 = next field to commit to LDS), rotated with constant indices.
-template <class B>
-struct HaloCopy {
-  uint32_t goffb[B::NQ];  // byte offset of this thread's halo-box points in a field (wrapped)
-  double v[kPrefetch][B::NQ];
-  __device__ __forceinline__ void init(int i0, int j0, int k0, const int n[3]) { offsets(i0, j0, k0, n, goffb); }
-  static __device__ __forceinline__ void offsets(int i0, int j0, int k0, const int n[3], uint32_t goffb[B::NQ]) {
-    // Most bricks' halo boxes lie inside the grid (82 % of the 16x4x4 bricks at 256^3): no
-    // wrap is needed there, and the choice is uniform over the workgroup.
-    const bool inside = i0 >= 3 && i0 + B::HX - 3 <= n[0] && j0 >= 3 && j0 + B::HY - 3 <= n[1] && k0 >= 3 &&
-                        k0 + B::HZ - 3 <= n[2];
-    if (inside) {
-      const int base = (i0 - 3) + n[0] * ((j0 - 3) + n[1] * (k0 - 3));
-#pragma unroll
-      for (int q = 0; q < B::NQ; ++q) {
-        const int e = threadIdx.x + 256 * q;
-        const int ee = e < B::NH ? e : 0;
-        const int hx = ee % B::HX, hy = (ee / B::HX) % B::HY, hz = ee / (B::HX * B::HY);
-        goffb[q] = 8u * (uint32_t)(base + hx + n[0] * (hy + n[1] * hz));
-      }
-      return;
-    }
-#pragma unroll
-    for (int q = 0; q < B::NQ; ++q) {
-      const int e = threadIdx.x + 256 * q;
-      const int ee = e < B::NH ? e : 0;
-      const int hx = ee % B::HX, hy = (ee / B::HX) % B::HY, hz = ee / (B::HX * B::HY);
-      // Brick origins lie inside the grid and n >= 8, so a halo coordinate lies in
-      // [-3, 3n): one conditional add and two conditional subtracts wrap it (cheaper
-      // than an integer remainder by a run-time n).
-      goffb[q] = 8u * (uint32_t)(wrap_halo(i0 + hx - 3, n[0]) +
-                                 n[0] * (wrap_halo(j0 + hy - 3, n[1]) + n[1] * wrap_halo(k0 + hz - 3, n[2])));
-    }
-  }
-  template <int SLOT>
-  __device__ __forceinline__ void fetch(const double* F, uint32_t nbytes) {
-    fetch_at<SLOT>(F, nbytes, goffb);
-  }
-  template <int SLOT>
-  __device__ __forceinline__ void fetch_at(const double* F, uint32_t nbytes, const uint32_t off[B::NQ]) {
-    static_assert(SLOT < kPrefetch, "ring slot");
-#pragma unroll
-    for (int q = 0; q < B::NQ; ++q)
-      v[SLOT][q] = bld(F, nbytes, off[q]);
-  }
-  __device__ __forceinline__ void commit_and_rotate(double* buf) {
-#pragma unroll
-    for (int q = 0; q < B::NQ; ++q)
-      buf[threadIdx.x + 256 * q] = v[0][q];
-#pragma unroll
-    for (int d = 0; d + 1 < kPrefetch; ++d)
-#pragma unroll
-      for (int q = 0; q < B::NQ; ++q) v[d][q] = v[d + 1][q];
-  }
-};
 
 // Halo box for staging by LDS-direct loads: x runs from i0 - 4 to i0 + BX + 3 (BX + 8 points,
 // one more on each side than the stencils need), so that with n0 even every aligned pair of
@@ -226,13 +121,13 @@ struct DBrick {
   static constexpr int NOFF = 2 * NR;  // two offset sets: fields with and without second derivatives
   static_assert(BX * BY * BZ == 256 && BX % 2 == 0, "one point per thread, even brick width");
 };
-constexpr int kRing = 5;      // LDS halo buffers of the direct-load ring (25 phases = 5 rounds of the ring)
-constexpr int kDmaAhead = 4;  // fields whose loads are in flight ahead of the one being processed
-// With the scalar field, its 10 source values at the point are loaded in phase kSrcPhase (the
-// second connection-function phase), three phases before the first use.
-constexpr int kSrcPhase = 10, kSrcLoads = 10;
-static_assert(NF % kRing == 0 && kDmaAhead == kRing - 1, "ring slot = phase mod kRing, across bricks");
 
+// The same as an instruction immediate chosen at compile time: at most N outstanding.
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt has 6 bits");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
 // Wait until at most n vector-memory operations of this wave are outstanding (expcnt and
 // lgkmcnt not waited on). Loads complete in issue order, so a load is complete once n newer
 // ones have been issued and the count drops to n.
@@ -301,539 +196,921 @@ struct HaloDma {
   }
 };
 
-// State carried from one brick to the next by a workgroup that walks several
-// bricks: the halo ring (the next fields to commit), the epilogue-operand ring
-// (slot d = phase + d) and the 25 values of the thread's point.
-// Halo staging of a brick type: a register ring (Brick) or LDS-direct loads (DBrick).
-template <class B> struct HaloOf { using type = HaloCopy<B>; static constexpr bool dma = false; };
-template <int BX, int BY, int BZ> struct HaloOf<DBrick<BX, BY, BZ>> {
-  using type = HaloDma<DBrick<BX, BY, BZ>>;
-  static constexpr bool dma = true;
-};
+// ---------------------------------------------------------------- the two roles of the stage kernel
+constexpr int kPairThreads = 512;  // waves 0-3: curvature waves, waves 4-7: transport waves, one point per thread of each
+constexpr int kIntervals = 13;     // barrier intervals per brick, two fields each (the last one)
+// Fields of interval i: kPairOrder[2 i] and kPairOrder[2 i + 1].
+constexpr int kPairOrder[2 * kIntervals] = {
+    F_BET, F_BET + 1, F_BET + 2, F_GT,  F_GT + 1, F_GT + 2, F_GT + 3, F_GT + 4, F_GT + 5, F_GAM, F_GAM + 1, F_GAM + 2, F_AT,
+    F_AT + 1, F_AT + 2, F_AT + 3, F_CHI, F_AT + 4, F_ALP, F_AT + 5, F_K, F_ET, F_ST, F_ST + 1, F_ST + 2, -1};
+// Fields with second and mixed derivatives: the shift, the conformal metric, chi and the lapse.
+constexpr bool pair_second(int f) {
+  return (f >= F_GT && f < F_GT + 6) || (f >= F_BET && f < F_BET + 3) || f == F_CHI || f == F_ALP;
+}
+constexpr int pair_fields(int i) { return kPairOrder[2 * i + 1] < 0 ? 1 : 2; }
 
-template <class B, class Pre>
-struct LdsCarry {
-  typename HaloOf<B>::type hc;
-  Pre ep[kEpiAhead + 1][4];
-  double cen[NF];
-};
-
-// The brick a workgroup processes next (valid is uniform): its halo offsets, this
-// thread's point in it (0 for a thread outside the grid), and the arrays and field
-// size of its grid (another run's in the batched form; the current ones otherwise).
+// LDS of a workgroup: a ring of three interval slots of two halo boxes each, then the exchange
+// (kExSlots values per point).
+constexpr int kExSlots = 10;
+// exchange, written in the last interval of the previous brick and read in interval 0 ...
+constexpr int EX_GI = 0, EX_P = 6, EX_IX = 7;
+// ... written in interval 9 (lapse), read in 10 and 11: chi (X_ij - gt_ij X / 3), D^i D_i alpha ...
+constexpr int EX_Y = 0, EX_D2A = 6;
+// ... written in interval 10, read in 11: the Gt^i right-hand side without advection and dissipation
+constexpr int EX_RG = 7;
 template <class B>
-struct NextBrick {
-  bool valid;
-  int c;
-  uint32_t goffb[B::NOFF];
-  const double* U;   // stage input
-  const double* un;  // RK4 epilogue operands
-  const double* acc;
-  size_t fs;
+struct PairRing {
+  static constexpr int FULL = B::NPAIR / 256;                   // load rounds of all four waves
+  static constexpr int LASTW = (B::NPAIR % 256 + 63) / 64;      // waves of the last, partial round
+  static constexpr int PB = 2 * (256 * FULL + 64 * LASTW);      // doubles per halo box
+  static constexpr int LDS = 6 * PB + kExSlots * 256;  // the sink's parked values, if any, follow
+  static_assert(LDS * 8 <= 160 * 1024, "LDS budget");
+  // One field's halo box into LDS by the curvature waves: FULL loads per lane, one more in the
+  // first LASTW waves.
+  static __device__ __forceinline__ void fetch(const double* F, uint32_t nbytes, double* buf, const uint32_t* off) {
+    const __amdgpu_buffer_rsrc_t r = field_rsrc(F, nbytes);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+    for (int q = 0; q < FULL; ++q)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          r, (__attribute__((address_space(3))) void*)(buf + 2 * (256 * q + 64 * w)), 16, off[q], 0, 0, 0);
+    if (LASTW && w < LASTW)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          r, (__attribute__((address_space(3))) void*)(buf + 2 * (256 * FULL + 64 * w)), 16, off[FULL], 0, 0, 0);
+  }
+  // Wait until at most K newer fields' loads of this (curvature) wave are outstanding.
+  template <int K>
+  static __device__ __forceinline__ void wait() {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (LASTW && w < LASTW)
+      wait_vmcnt<K*(FULL + 1)>();
+    else
+      wait_vmcnt<K * FULL>();
+  }
 };
 
-// Loads of the first brick of a workgroup (later bricks are prefetched during the
-// previous one): the epilogue operands of phases 0 .. kEpiAhead-1, the point's values, and
-// the first fields -- 0 .. kPrefetch-1 into the register ring, or with LDS-direct staging
-// 0 .. kDmaAhead-1 into ring slots 0 .. kDmaAhead-1 at `ring` (issued last, so that waiting
-// for the other loads does not wait for them).
-template <class B, class Sink, class Pre>
-__device__ __forceinline__ void lds_carry_fill(LdsCarry<B, Pre>& cy, const double* U, size_t fs, const Sink& sink,
-                                               int c, double* ring = nullptr) {
-  static_assert(kPrefetch >= 1 && kPrefetch <= 3, "ring depth");
-  const uint32_t nbytes = (uint32_t)(fs * 8);
-  if constexpr (!HaloOf<B>::dma) {
-    cy.hc.template fetch<0>(field_ptr(U, kStageOrder[0], fs), nbytes);
-    if constexpr (kPrefetch > 1) cy.hc.template fetch<(kPrefetch > 1 ? 1 : 0)>(field_ptr(U, kStageOrder[1], fs), nbytes);
-    if constexpr (kPrefetch > 2) cy.hc.template fetch<(kPrefetch > 2 ? 2 : 0)>(field_ptr(U, kStageOrder[2], fs), nbytes);
+// The halo-box points a lane of the curvature waves loads, in box coordinates, and their byte offsets
+// in a field for a given brick. Box points no stencil reads stand for a point of a line that is read
+// anyway (the two offset sets of HaloDma::offsets, whose selection this repeats in box coordinates),
+// packed five bits a coordinate, both sets in one word per load round: formed once per launch, so
+// that a brick costs a few multiply-adds per offset, plus the periodic wrap only where its box
+// crosses the grid's faces.
+template <class B>
+struct PairHalo {
+  static_assert(B::HX <= 32 && B::HY <= 32 && B::HZ <= 32, "five bits a coordinate");
+  uint32_t box[B::NR];      // second-derivative set in the low half, first-derivative set in the high half
+  uint32_t off[B::NOFF];    // byte offsets: [0, NR) the first set, [NR, 2 NR) the second
+  __device__ __forceinline__ void init() {
+#pragma unroll
+    for (int q = 0; q < B::NR; ++q) {
+      const int e = threadIdx.x + 256 * q;
+      const int ee = e < B::NPAIR ? e : 0;  // padding lanes load an in-box pair into the padding
+      const int hx = ee % B::NPR, y = (ee / B::NPR) % B::HY, z = ee / (B::NPR * B::HY);
+      const int dy = y - 3, dz = z - 3;
+      const bool yin = dy >= 0 && dy < B::Y, zin = dz >= 0 && dz < B::Z;
+      const bool y2 = dy >= -2 && dy < B::Y + 2, z2 = dz >= -2 && dz < B::Z + 2;
+      const int hi = min(max(hx, 2), B::NPR - 3);        // the pair moved into the brick's x-range
+      const int yc = min(max(dy, 0), B::Y - 1) + 3;      // the row moved inside the brick in y
+      const bool xh2 = (y2 && zin) || (yin && z2), row2 = yin || zin || (y2 && z2);
+      const bool xh1 = yin && zin, row1 = yin || zin;
+      const uint32_t lo = 2 * (xh2 ? hx : hi) | (row2 ? y : yc) << 5 | z << 10;
+      const uint32_t hi16 = 2 * (xh1 ? hx : hi) | (row1 ? y : yc) << 5 | z << 10;
+      box[q] = lo | hi16 << 16;
+    }
   }
+  // x in [-n, 3n) to its place in [0, n): the unsigned minimum keeps x - n only where it is not negative
+  static __device__ __forceinline__ int wrap(int x, int n) {
+    uint32_t u = (uint32_t)(x + n);
+    u = min(u, u - (uint32_t)n);
+    u = min(u, u - (uint32_t)n);
+    u = min(u, u - (uint32_t)n);
+    return (int)u;
+  }
+  __device__ __forceinline__ void locate(int i0, int j0, int k0, const int n[3]) {
+    // opaque per brick: the unpacked coordinates are formed here, not kept (and spilled) across bricks
 #pragma unroll
-  for (int d = 0; d < kEpiAhead; ++d)
+    for (int q = 0; q < B::NR; ++q) asm volatile("" : "+v"(box[q]));
+    const int x0 = i0 - 4, y0 = j0 - 3, z0 = k0 - 3;
+    if (x0 >= 0 && x0 + B::HX <= n[0] && y0 >= 0 && y0 + B::HY <= n[1] && z0 >= 0 && z0 + B::HZ <= n[2]) {  // uniform
+      const uint32_t base = (uint32_t)(x0 + n[0] * (y0 + n[1] * z0));
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (k < kPutCount[d]) cy.ep[d][k] = sink.preload_at(kPutField[d][k], c);
+      for (int q = 0; q < B::NOFF; ++q) {
+        const uint32_t b = box[q % B::NR] >> (q < B::NR ? 0 : 16);
+        off[q] = 8u * (base + (b & 31) + (uint32_t)n[0] * (((b >> 5) & 31) + (uint32_t)n[1] * ((b >> 10) & 31)));
+      }
+    } else {
 #pragma unroll
-  for (int f = 0; f < NF; ++f) cy.cen[f] = bld(field_ptr(U, f, fs), nbytes, (uint32_t)c * 8u);
-  if constexpr (HaloOf<B>::dma) {
+      for (int q = 0; q < B::NOFF; ++q) {
+        const uint32_t b = box[q % B::NR] >> (q < B::NR ? 0 : 16);
+        const int x = wrap(x0 + (int)(b & 31), n[0]), y = wrap(y0 + (int)((b >> 5) & 31), n[1]);
+        const int z = wrap(z0 + (int)((b >> 10) & 31), n[2]);
+        off[q] = 8u * (uint32_t)(x + n[0] * (y + n[1] * z));
+      }
+    }
+  }
+};
+
+// What a stage does for one brick, uniform over the workgroup: the arrays and field size of its
+// grid, the stage's time and RK4 weights, and the brick's origin.
+struct StageItem {
+  const double *U, *un;
+  double *acc, *out;
+  const double* F;  // point fluxes (or KT divergence) of U
+  double* Fn;       // where the point fluxes of `out` go (FUSE)
+  size_t fs;
+  double t, ca, cn;
+  int i0, j0, k0;
+};
+template <class B>
+__device__ __forceinline__ int pair_point(const StageItem& m, const int n[3], bool& active) {
+  const int pt = threadIdx.x & 255;
+  const int i = m.i0 + pt % B::X, j = m.j0 + (pt / B::X) % B::Y, k = m.k0 + pt / (B::X * B::Y);
+  active = i < n[0] && j < n[1] && k < n[2];
+  return active ? i + n[0] * (j + n[1] * k) : 0;
+}
+template <class B>
+__device__ __forceinline__ int pair_cidx() {
+  const int pt = threadIdx.x & 255;
+  return (pt % B::X + B::XO) + B::SY * (((pt / B::X) % B::Y + 3) + B::HY * (pt / (B::X * B::Y) + 3));
+}
+template <class B>
+__device__ __forceinline__ void flux_neighbours(const StageItem& m, const int n[3], int c, uint32_t fo[3][4]) {
+  constexpr int d[4] = {-2, -1, 1, 2};
+  const int st[3] = {1, n[0], n[0] * n[1]};
+  if (m.i0 >= 2 && m.i0 + B::X + 2 <= n[0] && m.j0 >= 2 && m.j0 + B::Y + 2 <= n[1] && m.k0 >= 2 &&
+      m.k0 + B::Z + 2 <= n[2]) {  // uniform
 #pragma unroll
-    for (int q = 0; q < kDmaAhead; ++q) cy.hc.fetch(field_ptr(U, kStageOrder[q], fs), nbytes, ring + q * B::NP);
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int o = 0; o < 4; ++o) fo[a][o] = 8u * (uint32_t)(c + d[o] * st[a]);
+  } else {
+    const int pt = threadIdx.x & 255;  // a thread outside the grid takes the neighbours of point 0, as c does
+    const int q[3] = {m.i0 + pt % B::X, m.j0 + (pt / B::X) % B::Y, m.k0 + pt / (B::X * B::Y)};
+    const bool in = q[0] < n[0] && q[1] < n[1] && q[2] < n[2];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int x = in ? q[a] : 0;
+#pragma unroll
+      for (int o = 0; o < 4; ++o) fo[a][o] = 8u * (uint32_t)(c + (wrap1(x + d[o], n[a]) - x) * st[a]);
+    }
+  }
+}
+// Loads for the divergence of conserved variable q: its fluxes at the neighbours, or (KT) the
+// divergence the pre-pass left.
+template <bool KT>
+__device__ __forceinline__ void pair_flux_load(const double* F, size_t fs, int c, const uint32_t fo[3][4], int q,
+                                               double v[3][4]) {
+  const uint32_t nb = (uint32_t)(fs * 8);
+  if constexpr (KT) {
+    v[0][0] = bld(field_at(F, q, fs), nb, (uint32_t)c * 8u);
+  } else {
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int o = 0; o < 4; ++o) v[a][o] = bld(field_at(F, 4 * a + q, fs), nb, fo[a][o]);
+  }
+}
+__device__ __forceinline__ int ring_next(int s) { return s == 2 ? 0 : s + 1; }
+__device__ __forceinline__ int ring_prev(int s) { return s == 0 ? 2 : s - 1; }
+// keeps the value in a register here: the arithmetic that forms it stays on this side of the next barrier
+__device__ __forceinline__ void pin(double& x) { asm volatile("" : "+v"(x)); }
+template <int I>
+using iv = std::integral_constant<int, I>;
+
+// Stencil taps of one field in registers. The roles load taps one batch ahead of the arithmetic that
+// uses them, with a scheduling fence after every batch: left to itself the compiler reads two or
+// three taps at a time and waits for each, about 25 LDS latencies per interval.
+__device__ __forceinline__ void fence() { __builtin_amdgcn_sched_barrier(0); }
+struct Lines {  // offsets -3..+3 along each axis (only the used ones are loaded)
+  double v[3][7];
+};
+template <class B>
+__device__ __forceinline__ void lines_load(const double* c, Lines& l) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) lds_line<B>(c, a, l.v[a]);
+}
+struct Cross {  // the 16 taps of a mixed derivative, [offset along a][offset along b] of -2, -1, 1, 2
+  double v[4][4];
+};
+template <class B>
+__device__ __forceinline__ void cross_load(const double* c, int a, int b, Cross& x) {
+  const int sa = a == 0 ? 1 : (a == 1 ? B::SY : B::SZ);
+  const int sb = b == 0 ? 1 : (b == 1 ? B::SY : B::SZ);
+  const int o[4] = {-2, -1, 1, 2};
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x.v[p][q] = c[o[p] * sa + o[q] * sb];
+}
+__device__ __forceinline__ double cross_value(const Cross& x, double i144) {
+  double in[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) in[p] = (x.v[p][0] - x.v[p][3]) + 8.0 * (x.v[p][2] - x.v[p][1]);
+  return ((in[0] - in[3]) + 8.0 * (in[2] - in[1])) * i144;
+}
+// First and (SECOND) pure second derivatives from the lines.
+template <bool SECOND>
+__device__ __forceinline__ void lines_derivs(const Lines& l, const DevParams& P, FieldDerivs& r) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    double none = 0.0;
+    op_line<SECOND, false, false>(l.v[a], 0.0, P.i12h[a], P.i12h2[a], 0.0, 0.0, r.d1[a], SECOND ? r.d2[S(a, a)] : none, none);
+  }
+}
+// The derivatives of an interval's two fields, K0 and K1 = 0 (not differentiated), 1 (first) or 2
+// (first and second): use0 / use1 take each as soon as it is there; between() runs while the first
+// taps arrive.
+template <class B, int K0, int K1, class Between, class Use0, class Use1>
+__device__ __forceinline__ void pair_derivs(const double* c0, const double* c1, const DevParams& P, Between between,
+                                            Use0 use0, Use1 use1) {
+  Lines l;
+  Cross x, y;
+  FieldDerivs d;
+  lines_load<B>(c0, l);
+  if constexpr (K0 == 2) cross_load<B>(c0, 0, 1, x);
+  fence();
+  between();
+  fence();
+  lines_derivs<K0 == 2>(l, P, d);
+  if constexpr (K0 == 2) {
+    cross_load<B>(c0, 0, 2, y);
+    fence();
+    d.d2[S(0, 1)] = cross_value(x, P.i144[0]);
+    cross_load<B>(c0, 1, 2, x);
+    fence();
+    d.d2[S(0, 2)] = cross_value(y, P.i144[1]);
+    if constexpr (K1 != 0) lines_load<B>(c1, l);
+    fence();
+    d.d2[S(1, 2)] = cross_value(x, P.i144[2]);
+    if constexpr (K1 == 2) cross_load<B>(c1, 0, 1, x);
+    fence();
+  } else if constexpr (K1 != 0) {
+    lines_load<B>(c1, l);
+    fence();
+  }
+  use0(d);
+  if constexpr (K1 != 0) {
+    fence();
+    FieldDerivs e;
+    lines_derivs<K1 == 2>(l, P, e);
+    if constexpr (K1 == 2) {
+      cross_load<B>(c1, 0, 2, y);
+      fence();
+      e.d2[S(0, 1)] = cross_value(x, P.i144[0]);
+      cross_load<B>(c1, 1, 2, x);
+      fence();
+      e.d2[S(0, 2)] = cross_value(y, P.i144[1]);
+      e.d2[S(1, 2)] = cross_value(x, P.i144[2]);
+    }
+    use1(e);
   }
 }
 
-// The whole right-hand side of one point with LDS-staged stencils. All threads
-// of the workgroup must call it (it contains barriers); `active` marks threads
-// whose point lies inside the grid. On entry `cy` holds this brick's ring,
-// epilogue operands and point values; if nx.valid, on return it holds those of
-// the next brick (loaded during the last phases of this one).
-// SC: the scalar field's source arrays (P.xsrc) are added in the K, At and Gt
-// equations: 0 none, 1 read through buffer descriptors (P.xsrc uniform in scalar
-// registers, a kernel argument), 2 read with plain loads (P.xsrc formed per work item).
-template <class B, bool KT, int SC, class Sink, class Pre>
-__device__ __forceinline__ void bssn_rhs_lds(const double* U, const double* F, size_t fs, const DevParams& P, double t,
-                                             int c, bool active, LdsCarry<B, Pre>& cy, const NextBrick<B>& nx,
-                                             double* buf0, double* buf1, Sink& sink, bool& prim_fail) {
-  struct {  // the per-point record, indexed by compile-time constants only (kept in registers)
-    double v[R3_COUNT];
-    __device__ __forceinline__ double& operator[](int k) { return v[k]; }
-  } R;
-  const int lx = threadIdx.x % B::X, ly = (threadIdx.x / B::X) % B::Y, lz = threadIdx.x / (B::X * B::Y);
-  const int cidx = (lx + B::XO) + B::SY * ((ly + 3) + B::HY * (lz + 3));
-  constexpr bool dma = HaloOf<B>::dma;  // LDS-direct staging: buf0 is the ring of kRing buffers
-  auto& hc = cy.hc;
-  auto& ep = cy.ep;
-  const uint32_t nbytes = (uint32_t)(fs * 8);
-  auto xsrc = [&](int q) -> double {  // source array q at this point (SC != 0)
-    if constexpr (SC == 1) return bld(field_ptr(P.xsrc, q, fs), nbytes, (uint32_t)c * 8u);
-    return P.xsrc[(size_t)q * fs + c];
-  };
+// First derivatives and the advection + dissipation of one field (the arithmetic of op_line with
+// the weights formed once per point).
+__device__ __forceinline__ void lines_transport(const Lines& l, const DevParams& P, const double wo[3],
+                                                const double wd[3], FieldDerivs& r) {
+  double acc = 0.0;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const double* v = l.v[a];
+    const double t1 = v[4] - v[2], t2 = v[5] - v[1];
+    r.d1[a] = (8.0 * t1 - t2) * P.i12h[a];
+    const double s1 = v[4] + v[2], s2 = v[5] + v[1];
+    const double d6 = ((v[6] + v[0]) - 6.0 * s2) + (15.0 * s1 - 20.0 * v[3]);
+    const double odd = ((v[6] - v[0]) - 6.0 * t2) + 21.0 * t1;
+    acc += wo[a] * odd;
+    acc += wd[a] * d6;
+  }
+  r.advko = acc;
+}
 
-  // centre values (registers); inactive threads hold a valid point's values and never store
-  const double chi = cy.cen[F_CHI];
-  const double ichi = 1.0 / chi;
-  const double K = cy.cen[F_K];
-  const double alpha = cy.cen[F_ALP];
-  double gt[6], beta[3], At[6], Gam[3];
+// Dissipation alone (the fluid of the centred scheme).
+__device__ __forceinline__ void lines_dissipation(const Lines& l, const DevParams& P, FieldDerivs& r) {
+  double acc = 0.0;
 #pragma unroll
-  for (int s = 0; s < 6; ++s) gt[s] = cy.cen[F_GT + s];
-#pragma unroll
-  for (int q = 0; q < 3; ++q) beta[q] = cy.cen[F_BET + q];
-#pragma unroll
-  for (int s = 0; s < 6; ++s) At[s] = cy.cen[F_AT + s];
-#pragma unroll
-  for (int q = 0; q < 3; ++q) Gam[q] = cy.cen[F_GAM + q];
+  for (int a = 0; a < 3; ++a) {
+    double d1, d2;
+    op_line<false, false, true>(l.v[a], 0.0, 0.0, 0.0, 0.0, P.iko[a], d1, d2, acc);
+  }
+  r.advko = acc;
+}
 
-  // epilogue operands of phase ph (of this brick, or of the next one when ph >= NF)
-  auto epi_load = [&](int ph, auto slot) {
-    if (ph < NF) {
+// Curvature waves. Seq walks the workgroup's bricks: first(m) / next(m) give the brick's StageItem
+// (false: none), P() the parameters of the run the last one belongs to, fail(bool) counts a point's
+// failed fluid recovery.
+template <class B, int SC, class Seq>
+__device__ __forceinline__ void curvature_waves(Seq& seq, double* smem) {
+  using R = PairRing<B>;
+  double* ex = smem + 6 * R::PB + threadIdx.x;
+  const int cidx = pair_cidx<B>();
+  PairHalo<B> halo;
+  StageItem m;
+  if (!seq.first(m)) return;  // uniform; the transport waves leave too
+  double gi[6];
+  double cv[11];  // chi, gt_ij, Et, St_i at the next brick's point
+  bool act;
+  // the point values of a brick, then its inverse metric and fluid recovery, handed to the transport waves
+  auto point_load = [&](const StageItem& q, const int n[3]) {
+    const uint32_t nb = (uint32_t)(q.fs * 8), c = 8u * (uint32_t)pair_point<B>(q, n, act);
+    cv[0] = bld(field_at(q.U, F_CHI, q.fs), nb, c);
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (k < kPutCount[ph]) ep[decltype(slot)::value][k] = sink.preload(kPutField[ph][k]);
-    } else if (nx.valid) {
+    for (int s = 0; s < 6; ++s) cv[1 + s] = bld(field_at(q.U, F_GT + s, q.fs), nb, c);
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (k < kPutCount[ph - NF])
-          ep[decltype(slot)::value][k] = sink.preload_from(kPutField[ph - NF][k], nx.c, nx.un, nx.acc, nx.fs);
-    }
+    for (int s = 0; s < 4; ++s) cv[7 + s] = bld(field_at(q.U, F_ET + s, q.fs), nb, c);
+    COSMOS_PHASE();
   };
-  {
-    double gi[6], St[3];
-    inv_sym(gt, gi);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) St[q] = cy.cen[F_ST + q];
+  double S3[3], Pr, iX;
+  auto point_setup = [&](double w) {
+    inv_sym(cv + 1, gi);
     Fluid fl;
-    prim_fail = active && recover(P.w, chi, gi, cy.cen[F_ET], St, fl);
+    seq.fail(recover(w, cv[0], gi, cv[7], cv + 8, fl) && act);
 #pragma unroll
-    for (int s = 0; s < 6; ++s) R[R3_GI + s] = gi[s];
-    R[R3_E] = fl.E;
-    R[R3_P] = fl.P;
-    R[R3_IX] = fl.invX;
+    for (int s = 0; s < 6; ++s) ex[(EX_GI + s) * 256] = gi[s];
+    ex[EX_P * 256] = Pr = fl.P;
+    ex[EX_IX * 256] = iX = fl.invX;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      R[R3_S + q] = fl.S[q];
-      R[R3_RG + q] = 0.0;
-      R[R3_SG + q] = 0.0;
+    for (int q = 0; q < 3; ++q) S3[q] = fl.S[q];
+  };
+  auto issue = [&](auto I, const StageItem& q, int slot) {  // the fields of interval I of brick q
+    constexpr int i = decltype(I)::value;
+    const uint32_t nb = (uint32_t)(q.fs * 8);
+    double* buf = smem + slot * (2 * R::PB);
+#pragma unroll
+    for (int k = 0; k < pair_fields(i); ++k) {
+      const int f = kPairOrder[2 * i + k];
+      R::fetch(field_at(q.U, f, q.fs), nb, buf + k * R::PB, pair_second(f) ? halo.off : halo.off + B::NR);
     }
-  }
-  if constexpr (dma) {
-    wait_vm(3 * B::NR);  // field 0 is in LDS once the loads of fields 1 .. 3, issued after it, remain
-  } else {
-    hc.commit_and_rotate(buf0);
-  }
+  };
+  int slot = 0;
+  point_load(m, seq.P().n);
+  halo.init();
+  halo.locate(m.i0, m.j0, m.k0, seq.P().n);
+  issue(iv<0>(), m, 0);
+  issue(iv<1>(), m, 1);
+  point_setup(seq.P().w);
+  R::template wait<2>();
   lds_barrier();
-
-  // Phase p processes field kStageOrder[p] from LDS buffer p & 1 (register ring: at its start
-  // the field p + kPrefetch is fetched into the last register slot, at its end the field p + 1
-  // is committed to the other buffer) or from ring slot p % kRing (LDS-direct: at its start the
-  // loads of field p + kDmaAhead go to slot (p - 1) % kRing, free since the last barrier; at its
-  // end the wave waits until field p + 1 has landed).
-  int phase = 0;
-  auto cur = [&]() -> const double* {
-    if constexpr (dma) return buf0 + (phase % kRing) * B::NP + cidx;
-    return ((phase & 1) ? buf1 : buf0) + cidx;
-  };
-  auto prefetch = [&]() {
-    if constexpr (dma) {
-      epi_load(phase + kEpiAhead, std::integral_constant<int, kEpiAhead>());
-      double* slot = buf0 + ((phase + kDmaAhead) % kRing) * B::NP;
-      if (phase + kDmaAhead < NF)
-        hc.fetch(field_ptr(U, kStageOrder[phase + kDmaAhead], fs), nbytes, slot, kSecondDerivs[phase + kDmaAhead]);
-      else if (nx.valid)
-        hc.fetch_at(field_ptr(nx.U, kStageOrder[phase + kDmaAhead - NF], nx.fs), (uint32_t)(nx.fs * 8), slot, nx.goffb);
-    } else {
-      if (phase + kPrefetch < NF)
-        hc.template fetch<kPrefetch - 1>(field_ptr(U, kStageOrder[phase + kPrefetch], fs), nbytes);
-      else if (nx.valid)
-        hc.template fetch_at<kPrefetch - 1>(field_ptr(nx.U, kStageOrder[phase + kPrefetch - NF], nx.fs),
-                                            (uint32_t)(nx.fs * 8), nx.goffb);
-      epi_load(phase + kEpiAhead, std::integral_constant<int, kEpiAhead>());
+  for (;;) {
+    const DevParams P = seq.P();
+    StageItem nx;
+    const double* cur;  // halo box of the interval's first field, at the thread's point
+    auto begin = [&](auto I) {
+      constexpr int i = decltype(I)::value;
+      if constexpr (i + 2 < kIntervals)
+        issue(iv<i + 2>(), m, ring_prev(slot));
+      else
+        issue(iv<i + 2 - kIntervals>(), nx, ring_prev(slot));
+    };
+    auto end = [&](auto I) {  // the next interval's fields have landed once only the newer ones remain
+      constexpr int i = decltype(I)::value;
+      R::template wait<pair_fields((i + 2) % kIntervals)>();
+      lds_barrier();
+      slot = ring_next(slot);
+      cur = smem + slot * (2 * R::PB) + cidx;
+      fence();
+    };
+    double DB[9], RG[3] = {0.0, 0.0, 0.0}, RX[6], G[18], gt[6];
+    auto shift = [&](int i, const FieldDerivs& d) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        DB[3 * i + a] = d.d1[a];
+        pin(DB[3 * i + a]);
+      }
+      RG[i] += contract_sym(gi, d.d2);
+#pragma unroll
+      for (int l = 0; l < 3; ++l) {
+        RG[l] += (gi[S(l, 0)] * d.d2[S(0, i)] + gi[S(l, 1)] * d.d2[S(1, i)] + gi[S(l, 2)] * d.d2[S(2, i)]) * (1.0 / 3.0);
+        pin(RG[l]);
+      }
+    };
+    auto metric = [&](int s, const FieldDerivs& d) {  // d_a gt_ij kept, -1/2 gt^lm d_l d_m gt_ij into R_ij
+      RX[s] = -0.5 * contract_sym(gi, d.d2);
+      pin(RX[s]);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        G[3 * s + a] = d.d1[a];
+        pin(G[3 * s + a]);
+      }
+    };
+    auto conn = [&](int k, const FieldDerivs& d) {  // gt_k(i d_j) Gt^k into R_ij
+#pragma unroll
+      for (int s = 0; s < 6; ++s) {
+        const int i = SI(s), j = SJ(s);
+        RX[s] += 0.5 * (gt[S(k, i)] * d.d1[j] + gt[S(k, j)] * d.d1[i]);
+        pin(RX[s]);
+      }
+    };
+    using D = const FieldDerivs&;
+    auto put = [&](auto I) { return [&, I] { begin(I); }; };  // this interval's loads two intervals ahead
+    cur = smem + slot * (2 * R::PB) + cidx;
+    pair_derivs<B, 2, 2>(cur, cur + R::PB, P, put(iv<0>()), [&](D d) { shift(0, d); }, [&](D d) { shift(1, d); });
+    end(iv<0>());
+    gt[0] = cur[R::PB];
+    pair_derivs<B, 2, 2>(cur, cur + R::PB, P, put(iv<1>()), [&](D d) { shift(2, d); }, [&](D d) { metric(0, d); });
+    end(iv<1>());
+    gt[1] = cur[0], gt[2] = cur[R::PB];
+    pair_derivs<B, 2, 2>(cur, cur + R::PB, P, put(iv<2>()), [&](D d) { metric(1, d); }, [&](D d) { metric(2, d); });
+    end(iv<2>());
+    gt[3] = cur[0], gt[4] = cur[R::PB];
+    pair_derivs<B, 2, 2>(cur, cur + R::PB, P, put(iv<3>()), [&](D d) { metric(3, d); }, [&](D d) { metric(4, d); });
+    end(iv<3>());
+    gt[5] = cur[0];
+    pair_derivs<B, 2, 1>(cur, cur + R::PB, P, put(iv<4>()), [&](D d) { metric(5, d); }, [&](D d) { conn(0, d); });
+    end(iv<4>());
+    pair_derivs<B, 1, 1>(cur, cur + R::PB, P, put(iv<5>()), [&](D d) { conn(1, d); }, [&](D d) { conn(2, d); });
+    double Gl[3][6];
+    {
+      double dgt[6][3];
+#pragma unroll
+      for (int q = 0; q < 18; ++q) dgt[q / 3][q % 3] = G[q];
+      connection_lower(dgt, Gl);
+#pragma unroll
+      for (int q = 0; q < 18; ++q) pin(Gl[q / 6][q % 6]);
     }
-  };
-  auto advance = [&](int) {
+    end(iv<5>());
+    double At[6], Gu[3][6], Gd[3];
+    begin(iv<6>());
+    At[0] = cur[0];
+    At[1] = cur[R::PB];
+    connection_raise(Gl, gi, Gu, Gd);
 #pragma unroll
-    for (int d = 0; d < kEpiAhead; ++d)
+    for (int q = 0; q < 18; ++q) pin(Gu[q / 6][q % 6]);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) ep[d][k] = ep[d + 1][k];
-    if constexpr (dma) {
-      // field phase + 1 was issued kDmaAhead - 1 phases ago; the phases since issued one field
-      // each, except past the brick's last field when there is no next brick
-      const int v = nx.valid ? 1 : 0;
-      const int newer = phase <= NF - 1 - kDmaAhead ? 3 : (phase == NF - kDmaAhead ? 2 + v : (phase == NF - 3 ? 1 + 2 * v : 3 * v));
-      // the scalar field's source loads, issued in phase kSrcPhase after that phase's halo
-      // loads, are newer than the field awaited at the end of the phases kSrcPhase .. kSrcPhase + 2
-      const int extra = (SC != 0 && phase >= kSrcPhase && phase < kSrcPhase + 3) ? kSrcLoads : 0;
-      wait_vm(newer * B::NR + extra);
-    } else {
-      if (phase + 1 < NF) hc.commit_and_rotate((phase & 1) ? buf0 : buf1);
+    for (int k = 0; k < 3; ++k) pin(Gd[k]);
+    end(iv<6>());
+    double xij[6], xj[3];
+    if constexpr (SC != 0) {  // older than this interval's halo loads, so the counted waits cover them
+      const uint32_t nb = (uint32_t)(m.fs * 8);
+      bool a;
+      const uint32_t c = 8u * (uint32_t)pair_point<B>(m, P.n, a);
+#pragma unroll
+      for (int q = 0; q < 6; ++q) xij[q] = bld(field_at(seq.xsrc(), SRC_SIJ + q, m.fs), nb, c);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) xj[q] = bld(field_at(seq.xsrc(), SRC_S + q, m.fs), nb, c);
+      COSMOS_PHASE();
     }
-    lds_barrier();
-    ++phase;
-  };
-  double Sup[3];  // S^j = chi gt^jk S_k
+    begin(iv<7>());
+    At[2] = cur[0];
+    At[3] = cur[R::PB];
+    ricci_quadratic(Gl, gi, Gu, Gd, RX);
 #pragma unroll
-  for (int j = 0; j < 3; ++j)
-    Sup[j] = chi * (R[R3_GI + S(j, 0)] * R[R3_S + 0] + R[R3_GI + S(j, 1)] * R[R3_S + 1] + R[R3_GI + S(j, 2)] * R[R3_S + 2]);
-  auto Sjk_at = [&](int s) { return Sup[SI(s)] * Sup[SJ(s)] * R[R3_IX] + R[R3_P] * chi * R[R3_GI + s]; };
-
-  // ---- shift
+    for (int s = 0; s < 6; ++s) pin(RX[s]);
+    end(iv<7>());
+    double dchi[3], ichi, chi;
+    At[4] = cur[R::PB];
+    chi = cur[0];
+    pair_derivs<B, 2, 0>(cur, nullptr, P, put(iv<8>()), [&](D d) {
+      ichi = 1.0 / chi;
+      ricci_conformal_factor(ichi, d.d1, d.d2, gt, gi, Gu, RX);
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    prefetch();
-    if (active) {
-      double gi[6];
+      for (int s = 0; s < 6; ++s) pin(RX[s]);
 #pragma unroll
-      for (int s = 0; s < 6; ++s) gi[s] = R[R3_GI + s];
-      FieldDerivs d;
-      lds_derivs<B, true, true>(cur(), P, beta, d);
+      for (int a = 0; a < 3; ++a) {
+        dchi[a] = d.d1[a];
+        pin(dchi[a]);
+      }
+    }, [](D) {});
+    end(iv<8>());
+    double dal[3], alpha;
+    At[5] = cur[R::PB];
+    alpha = cur[0];
+    pair_derivs<B, 2, 0>(cur, nullptr, P, put(iv<9>()), [&](D d) {
+      double cda = 0.0;
 #pragma unroll
-      for (int a = 0; a < 3; ++a) R[R3_DB + 3 * i + a] = d.d1[a];
-      R[R3_RG + i] += contract_sym(gi, d.d2);
+      for (int k = 0; k < 3; ++k)
 #pragma unroll
-      for (int l = 0; l < 3; ++l)
-        R[R3_RG + l] +=
-            (gi[S(l, 0)] * d.d2[S(0, i)] + gi[S(l, 1)] * d.d2[S(1, i)] + gi[S(l, 2)] * d.d2[S(2, i)]) * (1.0 / 3.0);
-      double r = 0.0;
-      if (P.evolve_shift) r = d.advko + (0.75 * Gam[i] - P.eta * beta[i]);
-      sink.put(F_BET + i, r, ep[0][0]);
+        for (int l = 0; l < 3; ++l) cda += gi[S(k, l)] * dchi[k] * d.d1[l];
+      const double ih = 0.5 * ichi;
+      double DDa[6], X[6];
+#pragma unroll
+      for (int s = 0; s < 6; ++s) {
+        const int i = SI(s), j = SJ(s);
+        DDa[s] = (d.d2[s] - (Gu[0][s] * d.d1[0] + Gu[1][s] * d.d1[1] + Gu[2][s] * d.d1[2])) +
+                 ih * ((dchi[i] * d.d1[j] + dchi[j] * d.d1[i]) - gt[s] * cda);
+      }
+      ex[EX_D2A * 256] = chi * contract_sym(gi, DDa);
+#pragma unroll
+      for (int s = 0; s < 6; ++s) {
+        double Sij = S3[SI(s)] * S3[SJ(s)] * iX + Pr * gt[s] * ichi;
+        if constexpr (SC != 0) Sij += xij[s];
+        X[s] = -DDa[s] + alpha * (RX[s] - 8.0 * PI_D * Sij);
+      }
+      const double trX3 = contract_sym(gi, X) * (1.0 / 3.0);
+#pragma unroll
+      for (int s = 0; s < 6; ++s) ex[(EX_Y + s) * 256] = chi * (X[s] - gt[s] * trX3);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        dal[a] = d.d1[a];
+        pin(dal[a]);
+      }
+    }, [](D) {});
+    end(iv<9>());
+    pair_derivs<B, 1, 0>(cur, nullptr, P, put(iv<10>()), [&](D d) {  // Gt^i: every term but advection and dissipation
+      double Amix[3][3], Aup[6];
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) Amix[k][j] = gi[S(k, 0)] * At[S(0, j)] + gi[S(k, 1)] * At[S(1, j)] + gi[S(k, 2)] * At[S(2, j)];
+#pragma unroll
+      for (int s = 0; s < 6; ++s) {
+        const int i = SI(s), j = SJ(s);
+        Aup[s] = Amix[i][0] * gi[S(0, j)] + Amix[i][1] * gi[S(1, j)] + Amix[i][2] * gi[S(2, j)];
+      }
+      const double divb = DB[0] + DB[4] + DB[8];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        double r = RG[i];
+        r -= (4.0 / 3.0) * alpha * (gi[S(i, 0)] * d.d1[0] + gi[S(i, 1)] * d.d1[1] + gi[S(i, 2)] * d.d1[2]);
+        r -= Gd[0] * DB[3 * i + 0] + Gd[1] * DB[3 * i + 1] + Gd[2] * DB[3 * i + 2];
+        r += (2.0 / 3.0) * Gd[i] * divb;
+        r -= 2.0 * (Aup[S(i, 0)] * dal[0] + Aup[S(i, 1)] * dal[1] + Aup[S(i, 2)] * dal[2]);
+        double inner = contract_sym(Gu[i], Aup);
+        inner -= (1.5 * ichi) * (Aup[S(i, 0)] * dchi[0] + Aup[S(i, 1)] * dchi[1] + Aup[S(i, 2)] * dchi[2]);
+        r += 2.0 * alpha * inner;
+        double Sj[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          Sj[j] = S3[j];
+          if constexpr (SC != 0) Sj[j] += xj[j];
+        }
+        r -= 16.0 * PI_D * alpha * (gi[S(i, 0)] * Sj[0] + gi[S(i, 1)] * Sj[1] + gi[S(i, 2)] * Sj[2]);
+        ex[(EX_RG + i) * 256] = r;
+      }
+    }, [](D) {});
+    end(iv<10>());
+    // the next brick: its point values (older than its halo loads) and offsets
+    if (!seq.next(nx)) {  // none: the transport waves' last two intervals
+      R::template wait<0>();
+      lds_barrier();
+      lds_barrier();
+      return;
     }
-    advance(0);
+    point_load(nx, seq.P().n);
+    halo.locate(nx.i0, nx.j0, nx.k0, seq.P().n);
+    begin(iv<11>());
+    end(iv<11>());
+    begin(iv<12>());
+    point_setup(seq.P().w);
+    end(iv<12>());
+    m = nx;
   }
+}
 
-  // ---- conformal metric
+// Transport waves: see the file's head. Sink<...> is the stage's epilogue.
+template <class B, bool KT, int SC, class Sink, class Seq>
+__device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
+  using R = PairRing<B>;
+  using Pre = typename Sink::Pre;
+  const double* ex = smem + 6 * R::PB + (threadIdx.x & 255);
+  double* nvals = smem + R::LDS + (threadIdx.x & 255);  // the sink's parked values
+  const int cidx = pair_cidx<B>();
+  StageItem m;
+  if (!seq.first(m)) return;  // uniform; the curvature waves leave too
+  double cen[NF];
+  bool active;
+  int c = pair_point<B>(m, seq.P().n, active);
+  auto centre_load = [&](const StageItem& q, int cp) {
+    const uint32_t nb = (uint32_t)(q.fs * 8);
 #pragma unroll
-  for (int s = 0; s < 6; ++s) {
-    prefetch();
-    if (active) {
-      double gi[6], db[3][3];
+    for (int f = 0; f < NF; ++f) cen[f] = bld(field_at(q.U, f, q.fs), nb, 8u * (uint32_t)cp);
+  };
+  centre_load(m, c);
+  int slot = 0;
+  lds_barrier();
+  for (;;) {
+    const DevParams P = seq.P();
+    Sink sink(m, c, active, P.alpha_collapse, nvals);
+    const double* cur;
+    auto end = [&](auto) {
+      lds_barrier();
+      slot = ring_next(slot);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    const double chi = cen[F_CHI], K = cen[F_K], alpha = cen[F_ALP];
+    const double c32 = chi * sqrt(chi), im32 = 1.0 / c32, ichi = 1.0 / chi;
+    double gt[6], beta[3], At[6], Gam[3], Sl[3], Sup[3];
 #pragma unroll
-      for (int q = 0; q < 6; ++q) gi[q] = R[R3_GI + q];
+    for (int s = 0; s < 6; ++s) gt[s] = cen[F_GT + s], At[s] = cen[F_AT + s];
+    const double E = c32 * cen[F_ET];
 #pragma unroll
-      for (int q = 0; q < 9; ++q) db[q / 3][q % 3] = R[R3_DB + q];
+    for (int q = 0; q < 3; ++q) beta[q] = cen[F_BET + q], Gam[q] = cen[F_GAM + q], Sl[q] = c32 * cen[F_ST + q];
+    // the inverse metric stays in the exchange (until interval 9) and is read where it is used
+    auto inverse = [&](double gi[6]) {
+#pragma unroll
+      for (int s = 0; s < 6; ++s) gi[s] = ex[(EX_GI + s) * 256];
+    };
+    const double Pr = ex[EX_P * 256], iX = ex[EX_IX * 256];
+    {
+      double gi[6];
+      inverse(gi);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) Sup[j] = chi * (gi[S(j, 0)] * Sl[0] + gi[S(j, 1)] * Sl[1] + gi[S(j, 2)] * Sl[2]);
+    }
+    // shift advection and dissipation along axis a: wo[a] odd differences + wd[a] 6th difference
+    double wo[3], wd[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      wo[a] = beta[a] * P.i24h[a];
+      wd[a] = fabs(beta[a]) * P.i24h[a];
+      wd[a] += P.iko[a];
+      pin(wo[a]);
+      pin(wd[a]);
+    }
+    auto Sjk_at = [&](int s) { return Sup[SI(s)] * Sup[SJ(s)] * iX + Pr * chi * ex[(EX_GI + s) * 256]; };
+
+    double DB[9], SG[3] = {0.0, 0.0, 0.0}, ag[3], pa[6], db[3][3];
+    double rb[3], rg[6];  // finished right-hand sides, stored one interval later
+    Pre eb[3], eg[6];
+    Lines l0, l1;
+    auto load0 = [&] {  // the interval's first field; the second with load1, at once where registers allow
+      cur = smem + slot * (2 * R::PB) + cidx;
+      lines_load<B>(cur, l0);
+      fence();
+    };
+    auto load1 = [&] {
+      lines_load<B>(cur + R::PB, l1);
+      fence();
+    };
+    auto load2 = [&] {
+      load0();
+      load1();
+    };
+    auto shift = [&](int i, const Lines& l) {
       FieldDerivs d;
-      lds_derivs<B, true, true>(cur(), P, beta, d);
+      lines_transport(l, P, wo, wd, d);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        DB[3 * i + a] = d.d1[a];
+        pin(DB[3 * i + a]);
+      }
+      rb[i] = 0.0;
+      if (P.evolve_shift) rb[i] = d.advko + (0.75 * Gam[i] - P.eta * beta[i]);
+      pin(rb[i]);
+    };
+    auto metric = [&](int s, const Lines& l) {
+      FieldDerivs d;
+      lines_transport(l, P, wo, wd, d);
       const double wsym = (s == 0 || s == 3 || s == 5) ? 1.0 : 2.0;
       const double Sjk = Sjk_at(s);
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        R[R3_GU + 3 * s + a] = d.d1[a];
-        R[R3_SG + a] += wsym * Sjk * d.d1[a];
+        SG[a] += wsym * Sjk * d.d1[a];
+        pin(SG[a]);
       }
-      R[R3_RX + s] = -0.5 * contract_sym(gi, d.d2);
       const int i = SI(s), j = SJ(s);
-      const double divb = db[0][0] + db[1][1] + db[2][2];
+      const double divb = DB[0] + DB[4] + DB[8];
       double r = d.advko;
 #pragma unroll
-      for (int k = 0; k < 3; ++k) r += gt[S(i, k)] * db[k][j] + gt[S(j, k)] * db[k][i];
+      for (int k = 0; k < 3; ++k) r += gt[S(i, k)] * DB[3 * k + j] + gt[S(j, k)] * DB[3 * k + i];
       r -= (2.0 / 3.0) * gt[s] * divb;
       r -= 2.0 * alpha * At[s];
-      sink.put(F_GT + s, r, ep[0][0]);
-    }
-    if (s == 5 && active) {  // connection and the quadratic Ricci terms (pure algebra)
-      COSMOS_PHASE();
-      double gi[6], dgt[6][3], Gu[3][6], Gd[3], Ric[6];
-#pragma unroll
-      for (int q = 0; q < 6; ++q) {
-        gi[q] = R[R3_GI + q];
-        Ric[q] = R[R3_RX + q];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) dgt[q][a] = R[R3_GU + 3 * q + a];
-      }
-      connection_and_quadratic_ricci(dgt, gi, Gu, Gd, Ric);
-#pragma unroll
-      for (int q = 0; q < 6; ++q) {
-        R[R3_RX + q] = Ric[q];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) R[R3_GU + 6 * k + q] = Gu[k][q];
-      }
-    }
-    advance(0);
-  }
-
-  // ---- connection functions
-  double xs[kSrcLoads];  // the scalar field's sources at this point: E + S, S_j, S_ij
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    prefetch();
-    if constexpr (SC != 0) {
-      if (9 + k == kSrcPhase) {  // every thread of the wave issues them (inactive ones hold a valid point)
-        xs[0] = xsrc(SRC_EPS);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) xs[1 + j] = xsrc(SRC_S + j);
-#pragma unroll
-        for (int q = 0; q < 6; ++q) xs[4 + q] = xsrc(SRC_SIJ + q);
-      }
-    }
-    if (active) {
+      rg[s] = r;
+      pin(rg[s]);
+    };
+    auto gamma = [&](int k, const Lines& l) {
       FieldDerivs d;
-      lds_derivs<B, false, true>(cur(), P, beta, d);
-      R[R3_RG + k] += d.advko;
+      lines_transport(l, P, wo, wd, d);
+      ag[k] = d.advko;
+      pin(ag[k]);
+    };
+    load2();
+    eb[0] = sink.preload(F_BET);
+    eb[1] = sink.preload(F_BET + 1);
+    fence();
+    shift(0, l0);
+    shift(1, l1);
+    end(iv<0>());
+    load2();
+    eb[2] = sink.preload(F_BET + 2);
+    eg[0] = sink.preload(F_GT);
+    sink.put(F_BET, rb[0], eb[0]);
+    sink.put(F_BET + 1, rb[1], eb[1]);
+    fence();
+    shift(2, l0);
+    metric(0, l1);
+    end(iv<1>());
+    load2();
+    eg[1] = sink.preload(F_GT + 1);
+    eg[2] = sink.preload(F_GT + 2);
+    sink.put(F_BET + 2, rb[2], eb[2]);
+    sink.put(F_GT, rg[0], eg[0]);
+    fence();
+    metric(1, l0);
+    metric(2, l1);
+    end(iv<2>());
+    load2();
+    eg[3] = sink.preload(F_GT + 3);
+    eg[4] = sink.preload(F_GT + 4);
+    sink.put(F_GT + 1, rg[1], eg[1]);
+    sink.put(F_GT + 2, rg[2], eg[2]);
+    fence();
+    metric(3, l0);
+    metric(4, l1);
+    end(iv<3>());
+    load2();
+    eg[5] = sink.preload(F_GT + 5);
+    sink.put(F_GT + 3, rg[3], eg[3]);
+    sink.put(F_GT + 4, rg[4], eg[4]);
+    fence();
+    metric(5, l0);
+    gamma(0, l1);
+    end(iv<4>());
+    double Amix[3][3], AK, EpS, KS = 0.0, sgt = 0.0;
+    load2();
+    sink.put(F_GT + 5, rg[5], eg[5]);
+    fence();
+    gamma(1, l0);
+    gamma(2, l1);
+    {  // the point algebra of the trace-K and fluid equations: S^jk K_jk and S^jk gt_jk, and K's source
+#pragma unroll
+      for (int s = 0; s < 6; ++s) {
+        const double Sjk = Sjk_at(s), wS = (s == 0 || s == 3 || s == 5 ? 1.0 : 2.0) * Sjk;
+        KS += wS * ((At[s] + gt[s] * K * (1.0 / 3.0)) * ichi);
+        sgt += wS * gt[s];
+      }
+      pin(KS);
+      pin(sgt);
+      double gi[6];
+      inverse(gi);
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          Amix[k][j] = gi[S(k, 0)] * At[S(0, j)] + gi[S(k, 1)] * At[S(1, j)] + gi[S(k, 2)] * At[S(2, j)];
+          pin(Amix[k][j]);
+        }
+      double Aup[6];
 #pragma unroll
       for (int s = 0; s < 6; ++s) {
         const int i = SI(s), j = SJ(s);
-        R[R3_RX + s] += 0.5 * (gt[S(k, i)] * d.d1[j] + gt[S(k, j)] * d.d1[i]);
+        Aup[s] = Amix[i][0] * gi[S(0, j)] + Amix[i][1] * gi[S(1, j)] + Amix[i][2] * gi[S(2, j)];
       }
+      const double AA = contract_sym(At, Aup);
+      const double Str = (Sup[0] * Sl[0] + Sup[1] * Sl[1] + Sup[2] * Sl[2]) * iX + 3.0 * Pr;
+      AK = AA + K * K * (1.0 / 3.0);
+      EpS = E + Str;
+      pin(AK);
+      pin(EpS);
     }
-    advance(0);
-  }
-
-  // ---- conformal factor
-  prefetch();
-  if (active) {
-    double gi[6], Gu[3][6], Ric[6];
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-      gi[q] = R[R3_GI + q];
-      Ric[q] = R[R3_RX + q];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) Gu[k][q] = R[R3_GU + 6 * k + q];
-    }
-    FieldDerivs d;
-    lds_derivs<B, true, true>(cur(), P, beta, d);
-    ricci_conformal_factor(ichi, d.d1, d.d2, gt, gi, Gu, Ric);
-#pragma unroll
-    for (int q = 0; q < 6; ++q) R[R3_RX + q] = Ric[q];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) R[R3_DCHI + a] = d.d1[a];
-    const double divb = R[R3_DB + 0] + R[R3_DB + 4] + R[R3_DB + 8];
-    sink.put(F_CHI, d.advko + (2.0 / 3.0) * chi * (alpha * K - divb), ep[0][0]);
-  }
-  advance(0);
-
-  // ---- lapse
-  prefetch();
-  if (active) {
-    double gi[6], Gu[3][6], dchi[3];
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-      gi[q] = R[R3_GI + q];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) Gu[k][q] = R[R3_GU + 6 * k + q];
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) dchi[a] = R[R3_DCHI + a];
-    FieldDerivs d;
-    lds_derivs<B, true, true>(cur(), P, beta, d);
-    const double* dal = d.d1;
-    double cda = 0.0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-      for (int l = 0; l < 3; ++l) cda += gi[S(k, l)] * dchi[k] * dal[l];
-    const double ih = 0.5 * ichi;
-    double DDa[6];
-#pragma unroll
-    for (int s = 0; s < 6; ++s) {
-      const int i = SI(s), j = SJ(s);
-      DDa[s] = (d.d2[s] - (Gu[0][s] * dal[0] + Gu[1][s] * dal[1] + Gu[2][s] * dal[2])) +
-               ih * ((dchi[i] * dal[j] + dchi[j] * dal[i]) - gt[s] * cda);
-    }
-    R[R3_D2A] = chi * contract_sym(gi, DDa);
-    const double Kbg = P.lapse_bg ? -3.0 * P.H0 / (1.0 + 2.0 * P.H0 * t) : 0.0;
-    sink.put(F_ALP, d.advko - 2.0 * alpha * (K - Kbg), ep[0][0]);
-    const double ix = R[R3_IX], pr = R[R3_P];
-#pragma unroll
-    for (int s = 0; s < 6; ++s) {
-      double Sij = R[R3_S + SI(s)] * R[R3_S + SJ(s)] * ix + pr * gt[s] * ichi;
-      if constexpr (SC != 0) Sij += xs[4 + s];
-      R[R3_RX + s] = -DDa[s] + alpha * (R[R3_RX + s] - 8.0 * PI_D * Sij);
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) R[R3_DAL + a] = dal[a];
-  }
-  advance(0);
-
-  // ---- trace K, and the final Gt^i right-hand side. Amix = gt^kl At_lj and one third of
-  // the trace gt^ij X_ij are kept for the At phases.
-  double Amix[3][3], trX3 = 0.0;
-  prefetch();
-  if (active) {
-    double gi[6];
-#pragma unroll
-    for (int q = 0; q < 6; ++q) gi[q] = R[R3_GI + q];
-    FieldDerivs d;
-    lds_derivs<B, false, true>(cur(), P, beta, d);
-    {
-      double X[6];
-#pragma unroll
-      for (int q = 0; q < 6; ++q) X[q] = R[R3_RX + q];
-      trX3 = contract_sym(gi, X) * (1.0 / 3.0);
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) Amix[k][j] = gi[S(k, 0)] * At[S(0, j)] + gi[S(k, 1)] * At[S(1, j)] + gi[S(k, 2)] * At[S(2, j)];
-    double Aup[6];
-#pragma unroll
-    for (int s = 0; s < 6; ++s) {
-      const int i = SI(s), j = SJ(s);
-      Aup[s] = Amix[i][0] * gi[S(0, j)] + Amix[i][1] * gi[S(1, j)] + Amix[i][2] * gi[S(2, j)];
-    }
-    const double AA = contract_sym(At, Aup);
-    const double Str = (Sup[0] * R[R3_S + 0] + Sup[1] * R[R3_S + 1] + Sup[2] * R[R3_S + 2]) * R[R3_IX] + 3.0 * R[R3_P];
-    double EpS = R[R3_E] + Str;
-    if constexpr (SC != 0) EpS += xs[0];
-    sink.put(F_K, d.advko + (-R[R3_D2A] + alpha * (AA + K * K * (1.0 / 3.0)) + 4.0 * PI_D * alpha * EpS), ep[0][0]);
-    // Gt^i: every remaining term
-    const double divb = R[R3_DB + 0] + R[R3_DB + 4] + R[R3_DB + 8];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      double Gu[6];
-#pragma unroll
-      for (int q = 0; q < 6; ++q) Gu[q] = R[R3_GU + 6 * i + q];
-      double Gd[3];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        double g[6];
-#pragma unroll
-        for (int q = 0; q < 6; ++q) g[q] = R[R3_GU + 6 * k + q];
-        Gd[k] = contract_sym(gi, g);
-      }
-      double r = R[R3_RG + i];
-      r -= (4.0 / 3.0) * alpha * (gi[S(i, 0)] * d.d1[0] + gi[S(i, 1)] * d.d1[1] + gi[S(i, 2)] * d.d1[2]);
-      r -= Gd[0] * R[R3_DB + 3 * i + 0] + Gd[1] * R[R3_DB + 3 * i + 1] + Gd[2] * R[R3_DB + 3 * i + 2];
-      r += (2.0 / 3.0) * Gd[i] * divb;
-      r -= 2.0 * (Aup[S(i, 0)] * R[R3_DAL + 0] + Aup[S(i, 1)] * R[R3_DAL + 1] + Aup[S(i, 2)] * R[R3_DAL + 2]);
-      double inner = contract_sym(Gu, Aup);
-      inner -= (1.5 * ichi) * (Aup[S(i, 0)] * R[R3_DCHI + 0] + Aup[S(i, 1)] * R[R3_DCHI + 1] + Aup[S(i, 2)] * R[R3_DCHI + 2]);
-      r += 2.0 * alpha * inner;
-      if constexpr (SC != 0) {
-        double Sj[3];
-#pragma unroll
-        for (int j = 0; j < 3; ++j) Sj[j] = R[R3_S + j] + xs[1 + j];
-        r -= 16.0 * PI_D * alpha * (gi[S(i, 0)] * Sj[0] + gi[S(i, 1)] * Sj[1] + gi[S(i, 2)] * Sj[2]);
-      } else {
-        r -= 16.0 * PI_D * alpha * (gi[S(i, 0)] * R[R3_S + 0] + gi[S(i, 1)] * R[R3_S + 1] + gi[S(i, 2)] * R[R3_S + 2]);
-      }
-      sink.put(F_GAM + i, r, ep[0][1 + i]);
-    }
-  }
-  advance(0);
-
-  // ---- traceless extrinsic curvature. The flux-divergence loads of conserved
-  // variable q (all three axes) are issued two phases before the phase that
-  // completes its right-hand side (q = 0 in At phase 4, 1 in At phase 5, 2 in the
-  // Et phase, 3 in the first St phase), so their latency overlaps the algebra.
-  double fa[3][4], fb[3][4];
-  constexpr bool kt = KT;  // divergence formed by the Kurganov-Tadmor pre-pass
-  Nbr fnb;
-  if (active) {
-    const int i = c % P.n[0], jk = c / P.n[0], j = jk % P.n[1], k = jk / P.n[1];
-    if (i >= 3 && i + 3 < P.n[0] && j >= 3 && j + 3 < P.n[1] && k >= 3 && k + 3 < P.n[2]) {
-      // no wrap: uniform over the interior bricks, most of the grid
-      const int sy = P.n[0], sz = P.n[0] * P.n[1];
-      fnb.base = c;
-#pragma unroll
-      for (int o = -3; o <= 3; ++o) {
-        fnb.d[0][o + 3] = o;
-        fnb.d[1][o + 3] = o * sy;
-        fnb.d[2][o + 3] = o * sz;
-      }
-    } else {
-      make_nbr(fnb, i, j, k, P.n);
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < 6; ++s) {
-    prefetch();
-    if (active) {
-      if (s == 4) flux_var_load(F, fs, c, fnb, 0, fa, kt);
-      if (s == 5) flux_var_load(F, fs, c, fnb, 1, fb, kt);
-      double db[3][3];
-#pragma unroll
-      for (int q = 0; q < 9; ++q) db[q / 3][q % 3] = R[R3_DB + q];
-      const int i = SI(s), j = SJ(s);
+    end(iv<5>());
+    auto curv = [&](int s, const Lines& l) {  // At_ij: every term but chi (X_ij - gt_ij X / 3)
       FieldDerivs d;
-      lds_derivs<B, false, true>(cur(), P, beta, d);
+      lines_transport(l, P, wo, wd, d);
+      const int i = SI(s), j = SJ(s);
       double r = d.advko;
 #pragma unroll
-      for (int k = 0; k < 3; ++k) r += At[S(i, k)] * db[k][j] + At[S(j, k)] * db[k][i];
-      r -= (2.0 / 3.0) * At[s] * (db[0][0] + db[1][1] + db[2][2]);
-      r += chi * (R[R3_RX + s] - gt[s] * trX3);
+      for (int k = 0; k < 3; ++k) r += At[S(i, k)] * DB[3 * k + j] + At[S(j, k)] * DB[3 * k + i];
+      r -= (2.0 / 3.0) * At[s] * (DB[0] + DB[4] + DB[8]);
       double AAij = 0.0;  // At_ik gt^kl At_lj
 #pragma unroll
       for (int k = 0; k < 3; ++k) AAij += At[S(i, k)] * Amix[k][j];
       r += alpha * (K * At[s] - 2.0 * AAij);
-      sink.put(F_AT + s, r, ep[0][0]);
-    }
-    advance(0);
-  }
-
-  // ---- fluid: flux divergence (from the pre-pass), sources, dissipation (KO only
-  // with the centred scheme: the Kurganov-Tadmor scheme carries its own)
-  const double nbeta[3] = {0.0, 0.0, 0.0};
-  const double im32 = 1.0 / (chi * sqrt(chi));
-  double sgt = 0.0;  // S^jk gt_jk (formed in the Et phase, used by the St phases)
-  prefetch();
-  if (active) {
-    const double div0 = flux_var_div(fa, P, kt);
-    flux_var_load(F, fs, c, fnb, 2, fa, kt);
-    double KS = 0.0;
-#pragma unroll
-    for (int s = 0; s < 6; ++s) {
-      const double Sjk = Sjk_at(s), wS = (s == 0 || s == 3 || s == 5 ? 1.0 : 2.0) * Sjk;
-      KS += wS * ((At[s] + gt[s] * K * (1.0 / 3.0)) * ichi);
-      sgt += wS * gt[s];
-    }
-    FieldDerivs d;
-    lds_derivs<B, false, false>(cur(), P, nbeta, d);
-    const double Sda = Sup[0] * R[R3_DAL + 0] + Sup[1] * R[R3_DAL + 1] + Sup[2] * R[R3_DAL + 2];
-    sink.put(F_ET, (kt ? 0.0 : d.advko) + (im32 * (alpha * KS - Sda) - div0), ep[0][0]);
-  }
-  advance(0);
-  double cnext[NF];  // the next brick's point values, loaded during the St phases
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    prefetch();
-    if (i == 0 && nx.valid) {
-#pragma unroll
-      for (int f = 0; f < NF; ++f) cnext[f] = bld(field_ptr(nx.U, f, nx.fs), (uint32_t)(nx.fs * 8), (uint32_t)nx.c * 8u);
-    }
-    if (active) {
-      // St_0: q = 1 (loaded in At phase 5), then issue q = 3; St_1: q = 2; St_2: q = 3
-      double divi;
-      if (i == 0) {
-        divi = flux_var_div(fb, P, kt);
-        flux_var_load(F, fs, c, fnb, 3, fb, kt);
-      } else {
-        divi = flux_var_div(i == 1 ? fa : fb, P, kt);
-      }
+      pa[s] = r;
+      pin(pa[s]);
+    };
+    load2();
+    fence();
+    curv(0, l0);
+    curv(1, l1);
+    end(iv<6>());
+    load2();
+    fence();
+    curv(2, l0);
+    curv(3, l1);
+    end(iv<7>());
+    double DCHI[3], DAL[3], rchi, ral;
+    uint32_t fo[3][4];  // byte offsets of the flux neighbours at -2, -1, +1, +2 along each axis
+    load0();
+    const Pre echi = sink.preload(F_CHI);
+    fence();
+    {
       FieldDerivs d;
-      lds_derivs<B, false, false>(cur(), P, nbeta, d);
-      double src = -R[R3_E] * R[R3_DAL + i] +
-                   (R[R3_S + 0] * R[R3_DB + 0 + i] + R[R3_S + 1] * R[R3_DB + 3 + i] + R[R3_S + 2] * R[R3_DB + 6 + i]);
-      src += 0.5 * alpha * (R[R3_SG + i] * ichi - sgt * R[R3_DCHI + i] * (ichi * ichi));
-      sink.put(F_ST + i, (kt ? 0.0 : d.advko) + (im32 * src - divi), ep[0][0]);
+      lines_transport(l0, P, wo, wd, d);
+      const double divb = DB[0] + DB[4] + DB[8];
+      rchi = d.advko + (2.0 / 3.0) * chi * (alpha * K - divb);
+      pin(rchi);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        DCHI[a] = d.d1[a];
+        pin(DCHI[a]);
+      }
     }
-    if (i < 2) advance(0);
-  }
-  if (nx.valid) {  // hand over to the next brick: the halo ring already holds its first fields
+    load1();
+    curv(4, l1);
+    if constexpr (!KT) flux_neighbours<B>(m, P.n, c, fo);
+    end(iv<8>());
+    double f0[3][4], f1[3][4];
+    double eps = 0.0;
+    load0();
+    const Pre eal = sink.preload(F_ALP);
+    Pre ea[6];
 #pragma unroll
-    for (int f = 0; f < NF; ++f) cy.cen[f] = cnext[f];
+    for (int s = 0; s < 3; ++s) ea[s] = sink.preload(F_AT + s);
+    pair_flux_load<KT>(m.F, m.fs, c, fo, 0, f0);
+    if constexpr (SC != 0) eps = bld(field_at(seq.xsrc(), SRC_EPS, m.fs), (uint32_t)(m.fs * 8), 8u * (uint32_t)c);
+    sink.put(F_CHI, rchi, echi);
+    fence();
+    {
+      FieldDerivs d;
+      lines_transport(l0, P, wo, wd, d);
+      const double Kbg = P.lapse_bg ? -3.0 * P.H0 / (1.0 + 2.0 * P.H0 * m.t) : 0.0;
+      ral = d.advko - 2.0 * alpha * (K - Kbg);
+      pin(ral);
 #pragma unroll
-    for (int q = 0; q < B::NOFF; ++q) hc.goffb[q] = nx.goffb[q];
+      for (int a = 0; a < 3; ++a) {
+        DAL[a] = d.d1[a];
+        pin(DAL[a]);
+      }
+    }
+    load1();
+    curv(5, l1);
+    end(iv<9>());
+    double rk, ret;
+    load0();
+    const Pre ek = sink.preload(F_K), eet = sink.preload(F_ET);
 #pragma unroll
-    for (int d = 0; d < kEpiAhead; ++d)
+    for (int s = 3; s < 6; ++s) ea[s] = sink.preload(F_AT + s);
+    pair_flux_load<KT>(m.F, m.fs, c, fo, 1, f1);
+    sink.put(F_ALP, ral, eal);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) ep[d][k] = ep[d + 1][k];
+    for (int s = 0; s < 3; ++s) sink.put(F_AT + s, pa[s] + ex[(EX_Y + s) * 256], ea[s]);
+    fence();
+    {
+      FieldDerivs d;
+      lines_transport(l0, P, wo, wd, d);
+      if constexpr (SC != 0) EpS += eps;
+      rk = d.advko + (-ex[EX_D2A * 256] + alpha * AK + 4.0 * PI_D * alpha * EpS);
+      pin(rk);
+    }
+    {
+      load1();
+      const double div0 = flux_var_div(f0, P, KT);
+      FieldDerivs d;
+      if constexpr (!KT) lines_dissipation(l1, P, d);
+      const double Sda = Sup[0] * DAL[0] + Sup[1] * DAL[1] + Sup[2] * DAL[2];
+      ret = (KT ? 0.0 : d.advko) + (im32 * (alpha * KS - Sda) - div0);
+      pin(ret);
+    }
+    pair_flux_load<KT>(m.F, m.fs, c, fo, 2, f0);
+    end(iv<10>());
+    double rs[3];
+    auto momentum = [&](int i, const Lines& l, const double f[3][4]) {
+      const double divi = flux_var_div(f, P, KT);
+      FieldDerivs d;
+      if constexpr (!KT) lines_dissipation(l, P, d);
+      double src = -E * DAL[i] + (Sl[0] * DB[0 + i] + Sl[1] * DB[3 + i] + Sl[2] * DB[6 + i]);
+      src += 0.5 * alpha * (SG[i] * ichi - sgt * DCHI[i] * (ichi * ichi));
+      rs[i] = (KT ? 0.0 : d.advko) + (im32 * src - divi);
+      pin(rs[i]);
+    };
+    load0();
+    Pre es[3], em[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) em[k] = sink.preload(F_GAM + k);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) es[k] = sink.preload(F_ST + k);
+    sink.put(F_K, rk, ek);
+    sink.put(F_ET, ret, eet);
+#pragma unroll
+    for (int s = 3; s < 6; ++s) sink.put(F_AT + s, pa[s] + ex[(EX_Y + s) * 256], ea[s]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      ag[k] += ex[(EX_RG + k) * 256];
+      pin(ag[k]);
+    }
+    fence();
+    momentum(0, l0, f1);
+    load1();
+    pair_flux_load<KT>(m.F, m.fs, c, fo, 3, f1);
+    momentum(1, l1, f0);
+    end(iv<11>());
+    load0();
+    es[2] = sink.preload(F_ST + 2);
+    StageItem nx;
+    bool nact = false;
+    int nc = 0;
+    const bool more = seq.peek(nx, nc, nact);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) sink.put(F_GAM + k, ag[k], em[k]);
+    sink.put(F_ST, rs[0], es[0]);
+    sink.put(F_ST + 1, rs[1], es[1]);
+    fence();
+    momentum(2, l0, f1);
+    if (more) {
+      centre_load(nx, nc);
+    } else {  // so that the old values do not stay live for this case
+#pragma unroll
+      for (int f = 0; f < NF; ++f) cen[f] = 0.0;
+    }
+    sink.put(F_ST + 2, rs[2], es[2]);
+    sink.finish(m, P, seq);
+    end(iv<12>());
+    if (!more) return;
+    m = nx;
+    c = nc;
+    active = nact;
+    seq.advance();
   }
 }
 
