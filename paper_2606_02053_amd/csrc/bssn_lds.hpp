@@ -522,6 +522,7 @@ __device__ __forceinline__ void curvature_waves(Seq& seq, double* smem) {
   };
   double S3[3], Pr, iX;
   auto point_setup = [&](double w) {
+    asm volatile("" : "+v"(w));  // 1 + w and 4 w are formed here, not kept (and spilled) across bricks
     inv_sym(cv + 1, gi);
     Fluid fl;
     seq.fail(recover(w, cv[0], gi, cv[7], cv + 8, fl) && act);
@@ -640,16 +641,6 @@ __device__ __forceinline__ void curvature_waves(Seq& seq, double* smem) {
     for (int k = 0; k < 3; ++k) pin(Gd[k]);
     end(iv<6>());
     double xij[6], xj[3];
-    if constexpr (SC != 0) {  // older than this interval's halo loads, so the counted waits cover them
-      const uint32_t nb = (uint32_t)(m.fs * 8);
-      bool a;
-      const uint32_t c = 8u * (uint32_t)pair_point<B>(m, P.n, a);
-#pragma unroll
-      for (int q = 0; q < 6; ++q) xij[q] = bld(field_at(seq.xsrc(), SRC_SIJ + q, m.fs), nb, c);
-#pragma unroll
-      for (int q = 0; q < 3; ++q) xj[q] = bld(field_at(seq.xsrc(), SRC_S + q, m.fs), nb, c);
-      COSMOS_PHASE();
-    }
     begin(iv<7>());
     At[2] = cur[0];
     At[3] = cur[R::PB];
@@ -658,6 +649,15 @@ __device__ __forceinline__ void curvature_waves(Seq& seq, double* smem) {
     for (int s = 0; s < 6; ++s) pin(RX[s]);
     end(iv<7>());
     double dchi[3], ichi, chi;
+    // The scalar field's sources, an interval before their use; issued before the interval's halo loads,
+    // so the counted waits cover them.
+    bool inside;
+    const uint32_t cb = SC != 0 ? 8u * (uint32_t)pair_point<B>(m, P.n, inside) : 0u;
+    if constexpr (SC != 0) {
+#pragma unroll
+      for (int q = 0; q < 6; ++q) xij[q] = bld(field_at(seq.xsrc(), SRC_SIJ + q, m.fs), (uint32_t)(m.fs * 8), cb);
+      COSMOS_PHASE();
+    }
     At[4] = cur[R::PB];
     chi = cur[0];
     pair_derivs<B, 2, 0>(cur, nullptr, P, put(iv<8>()), [&](D d) {
@@ -673,6 +673,11 @@ __device__ __forceinline__ void curvature_waves(Seq& seq, double* smem) {
     }, [](D) {});
     end(iv<8>());
     double dal[3], alpha;
+    if constexpr (SC != 0) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) xj[q] = bld(field_at(seq.xsrc(), SRC_S + q, m.fs), (uint32_t)(m.fs * 8), cb);
+      COSMOS_PHASE();
+    }
     At[5] = cur[R::PB];
     alpha = cur[0];
     pair_derivs<B, 2, 0>(cur, nullptr, P, put(iv<9>()), [&](D d) {
@@ -819,9 +824,15 @@ __device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
     }
     auto Sjk_at = [&](int s) { return Sup[SI(s)] * Sup[SJ(s)] * iX + Pr * chi * ex[(EX_GI + s) * 256]; };
 
-    double DB[9], SG[3] = {0.0, 0.0, 0.0}, ag[3], pa[6], db[3][3];
-    double rb[3], rg[6];  // finished right-hand sides, stored one interval later
+    double DB[9], SG[3] = {0.0, 0.0, 0.0};
+    // right-hand sides waiting for their epilogue operand (stored one interval later)
+    using Hold = typename Sink::Hold;
+    Hold rb[3], rg[6], ag[3], pa[6];
     Pre eb[3], eg[6];
+    auto keep = [&](Hold& h, double k, double uc) {
+      h = sink.hold(k, uc);
+      pin(h.a);
+    };
     Lines l0, l1;
     auto load0 = [&] {  // the interval's first field; the second with load1, at once where registers allow
       cur = smem + slot * (2 * R::PB) + cidx;
@@ -844,9 +855,9 @@ __device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
         DB[3 * i + a] = d.d1[a];
         pin(DB[3 * i + a]);
       }
-      rb[i] = 0.0;
-      if (P.evolve_shift) rb[i] = d.advko + (0.75 * Gam[i] - P.eta * beta[i]);
-      pin(rb[i]);
+      double r = 0.0;
+      if (P.evolve_shift) r = d.advko + (0.75 * Gam[i] - P.eta * beta[i]);
+      keep(rb[i], r, l.v[0][3]);
     };
     auto metric = [&](int s, const Lines& l) {
       FieldDerivs d;
@@ -865,20 +876,19 @@ __device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
       for (int k = 0; k < 3; ++k) r += gt[S(i, k)] * DB[3 * k + j] + gt[S(j, k)] * DB[3 * k + i];
       r -= (2.0 / 3.0) * gt[s] * divb;
       r -= 2.0 * alpha * At[s];
-      rg[s] = r;
-      pin(rg[s]);
+      keep(rg[s], r, l.v[0][3]);
     };
     auto gamma = [&](int k, const Lines& l) {
       FieldDerivs d;
       lines_transport(l, P, wo, wd, d);
-      ag[k] = d.advko;
-      pin(ag[k]);
+      keep(ag[k], d.advko, l.v[0][3]);
     };
-    load2();
+    load0();
     eb[0] = sink.preload(F_BET);
     eb[1] = sink.preload(F_BET + 1);
     fence();
     shift(0, l0);
+    load1();
     shift(1, l1);
     end(iv<0>());
     load2();
@@ -966,8 +976,7 @@ __device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) AAij += At[S(i, k)] * Amix[k][j];
       r += alpha * (K * At[s] - 2.0 * AAij);
-      pa[s] = r;
-      pin(pa[s]);
+      keep(pa[s], r, l.v[0][3]);
     };
     load2();
     fence();
@@ -979,7 +988,8 @@ __device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
     curv(2, l0);
     curv(3, l1);
     end(iv<7>());
-    double DCHI[3], DAL[3], rchi, ral;
+    double DCHI[3], DAL[3];
+    Hold rchi, ral;
     uint32_t fo[3][4];  // byte offsets of the flux neighbours at -2, -1, +1, +2 along each axis
     load0();
     const Pre echi = sink.preload(F_CHI);
@@ -988,8 +998,7 @@ __device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
       FieldDerivs d;
       lines_transport(l0, P, wo, wd, d);
       const double divb = DB[0] + DB[4] + DB[8];
-      rchi = d.advko + (2.0 / 3.0) * chi * (alpha * K - divb);
-      pin(rchi);
+      keep(rchi, d.advko + (2.0 / 3.0) * chi * (alpha * K - divb), chi);
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         DCHI[a] = d.d1[a];
@@ -1007,7 +1016,6 @@ __device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
     Pre ea[6];
 #pragma unroll
     for (int s = 0; s < 3; ++s) ea[s] = sink.preload(F_AT + s);
-    pair_flux_load<KT>(m.F, m.fs, c, fo, 0, f0);
     if constexpr (SC != 0) eps = bld(field_at(seq.xsrc(), SRC_EPS, m.fs), (uint32_t)(m.fs * 8), 8u * (uint32_t)c);
     sink.put(F_CHI, rchi, echi);
     fence();
@@ -1015,8 +1023,7 @@ __device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
       FieldDerivs d;
       lines_transport(l0, P, wo, wd, d);
       const double Kbg = P.lapse_bg ? -3.0 * P.H0 / (1.0 + 2.0 * P.H0 * m.t) : 0.0;
-      ral = d.advko - 2.0 * alpha * (K - Kbg);
-      pin(ral);
+      keep(ral, d.advko - 2.0 * alpha * (K - Kbg), alpha);
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         DAL[a] = d.d1[a];
@@ -1025,8 +1032,9 @@ __device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
     }
     load1();
     curv(5, l1);
+    pair_flux_load<KT>(m.F, m.fs, c, fo, 0, f0);
     end(iv<9>());
-    double rk, ret;
+    Hold rk, ret;
     load0();
     const Pre ek = sink.preload(F_K), eet = sink.preload(F_ET);
 #pragma unroll
@@ -1034,14 +1042,16 @@ __device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
     pair_flux_load<KT>(m.F, m.fs, c, fo, 1, f1);
     sink.put(F_ALP, ral, eal);
 #pragma unroll
-    for (int s = 0; s < 3; ++s) sink.put(F_AT + s, pa[s] + ex[(EX_Y + s) * 256], ea[s]);
+    for (int s = 0; s < 3; ++s) {
+      sink.more(pa[s], ex[(EX_Y + s) * 256]);
+      sink.put(F_AT + s, pa[s], ea[s]);
+    }
     fence();
     {
       FieldDerivs d;
       lines_transport(l0, P, wo, wd, d);
       if constexpr (SC != 0) EpS += eps;
-      rk = d.advko + (-ex[EX_D2A * 256] + alpha * AK + 4.0 * PI_D * alpha * EpS);
-      pin(rk);
+      keep(rk, d.advko + (-ex[EX_D2A * 256] + alpha * AK + 4.0 * PI_D * alpha * EpS), K);
     }
     {
       load1();
@@ -1049,20 +1059,18 @@ __device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
       FieldDerivs d;
       if constexpr (!KT) lines_dissipation(l1, P, d);
       const double Sda = Sup[0] * DAL[0] + Sup[1] * DAL[1] + Sup[2] * DAL[2];
-      ret = (KT ? 0.0 : d.advko) + (im32 * (alpha * KS - Sda) - div0);
-      pin(ret);
+      keep(ret, (KT ? 0.0 : d.advko) + (im32 * (alpha * KS - Sda) - div0), l1.v[0][3]);
     }
     pair_flux_load<KT>(m.F, m.fs, c, fo, 2, f0);
     end(iv<10>());
-    double rs[3];
+    Hold rs[3];
     auto momentum = [&](int i, const Lines& l, const double f[3][4]) {
       const double divi = flux_var_div(f, P, KT);
       FieldDerivs d;
       if constexpr (!KT) lines_dissipation(l, P, d);
       double src = -E * DAL[i] + (Sl[0] * DB[0 + i] + Sl[1] * DB[3 + i] + Sl[2] * DB[6 + i]);
       src += 0.5 * alpha * (SG[i] * ichi - sgt * DCHI[i] * (ichi * ichi));
-      rs[i] = (KT ? 0.0 : d.advko) + (im32 * src - divi);
-      pin(rs[i]);
+      keep(rs[i], (KT ? 0.0 : d.advko) + (im32 * src - divi), l.v[0][3]);
     };
     load0();
     Pre es[3], em[3];
@@ -1073,11 +1081,14 @@ __device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
     sink.put(F_K, rk, ek);
     sink.put(F_ET, ret, eet);
 #pragma unroll
-    for (int s = 3; s < 6; ++s) sink.put(F_AT + s, pa[s] + ex[(EX_Y + s) * 256], ea[s]);
+    for (int s = 3; s < 6; ++s) {
+      sink.more(pa[s], ex[(EX_Y + s) * 256]);
+      sink.put(F_AT + s, pa[s], ea[s]);
+    }
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      ag[k] += ex[(EX_RG + k) * 256];
-      pin(ag[k]);
+      sink.more(ag[k], ex[(EX_RG + k) * 256]);
+      pin(ag[k].a);
     }
     fence();
     momentum(0, l0, f1);

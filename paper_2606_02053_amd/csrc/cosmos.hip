@@ -184,7 +184,7 @@ struct FluxPair {
             unsigned long long* status) {
     bool wrote = false;
     const int rc = launch_stage(p, T, s, U, cur, un, acc, out, fs, P, t, ca, cn, mode, status,
-                                (mode == 1 || mode == 2 || (mode == 3 && chain)) ? nxt : nullptr, ready, &wrote);
+                                (mode >= 1 && (mode < 4 || chain)) ? nxt : nullptr, ready, &wrote);
     if (wrote) std::swap(cur, nxt);
     ready = wrote;
     return rc;
@@ -211,11 +211,11 @@ int rk4_step(const cosmos_grid* grid, const cosmos_params* params, double t, dou
   hipStream_t s = (hipStream_t)stream;
   FluxPair own{F, (double*)(w + L.F2)};
   FluxPair& fx = carry ? *carry : own;
-  if ((rc = fx.stage(params, T, s, u, u, acc, U2, fs, P, t, dt / 6.0, dt / 2.0, 1, status))) return rc;
-  fx.stage(params, T, s, U2, u, acc, U3, fs, P, t + dt / 2.0, dt / 3.0, dt / 2.0, 2, status);
-  fx.stage(params, T, s, U3, u, acc, U4, fs, P, t + dt / 2.0, dt / 3.0, dt, 2, status);
+  if ((rc = fx.stage(params, T, s, u, u, acc, U2, fs, P, t, 0.0, dt / 2.0, 1, status))) return rc;
+  fx.stage(params, T, s, U2, u, acc, U3, fs, P, t + dt / 2.0, 0.0, dt / 2.0, 2, status);
+  fx.stage(params, T, s, U3, u, acc, U4, fs, P, t + dt / 2.0, 0.0, dt, 3, status);
   // the last stage writes u_{n+1} over u, or into unew (u itself then keeps u_n)
-  fx.stage(params, T, s, U4, nullptr, acc, unew ? unew : u, fs, P, t + dt, dt / 6.0, 0.0, 3, status);
+  fx.stage(params, T, s, U4, nullptr, acc, unew ? unew : u, fs, P, t + dt, dt / 6.0, 0.0, 4, status);
   HIP_TRY(hipGetLastError());
   return COSMOS_OK;
 }
