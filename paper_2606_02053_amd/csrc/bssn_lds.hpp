@@ -63,36 +63,71 @@ __device__ __forceinline__ void lds_line(const double* c, int a, double v[7]) {
   for (int o = 0; o < 7; ++o) v[o] = c[(o - 3) * st];
 }
 
+// Stencil taps of one field in registers. Taps are loaded one batch ahead of the arithmetic that uses
+// them, with a scheduling fence after every batch: left to itself the compiler reads two or three taps
+// at a time and waits for each, about a dozen LDS latencies per field with second derivatives.
+__device__ __forceinline__ void fence() { __builtin_amdgcn_sched_barrier(0); }
+struct Lines {  // offsets -3..+3 along each axis (only the used ones are loaded)
+  double v[3][7];
+};
 template <class B>
-__device__ __forceinline__ double lds_mixed(const double* c, int a, int b, double i144) {
+__device__ __forceinline__ void lines_load(const double* c, Lines& l) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) lds_line<B>(c, a, l.v[a]);
+}
+struct Cross {  // the 16 taps of a mixed derivative, [offset along a][offset along b] of -2, -1, 1, 2
+  double v[4][4];
+};
+template <class B>
+__device__ __forceinline__ void cross_load(const double* c, int a, int b, Cross& x) {
   const int sa = a == 0 ? 1 : (a == 1 ? B::SY : B::SZ);
   const int sb = b == 0 ? 1 : (b == 1 ? B::SY : B::SZ);
-  const int oa[4] = {-2, -1, 1, 2};
+  const int o[4] = {-2, -1, 1, 2};
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x.v[p][q] = c[o[p] * sa + o[q] * sb];
+}
+__device__ __forceinline__ double cross_value(const Cross& x, double i144) {
   double in[4];
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    const double* r = c + oa[p] * sa;
-    in[p] = (r[-2 * sb] - r[2 * sb]) + 8.0 * (r[sb] - r[-sb]);
-  }
+  for (int p = 0; p < 4; ++p) in[p] = (x.v[p][0] - x.v[p][3]) + 8.0 * (x.v[p][2] - x.v[p][1]);
   return ((in[0] - in[3]) + 8.0 * (in[2] - in[1])) * i144;
 }
-
-template <class B, bool SECOND, bool ADV, bool KO = true>
+// First and (SECOND) pure second derivatives from the lines.
+template <bool SECOND>
+__device__ __forceinline__ void lines_derivs(const Lines& l, const DevParams& P, FieldDerivs& r) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    double none = 0.0;
+    op_line<SECOND, false, false>(l.v[a], 0.0, P.i12h[a], P.i12h2[a], 0.0, 0.0, r.d1[a], SECOND ? r.d2[S(a, a)] : none, none);
+  }
+}
+// All derivatives of one staged field: first (and SECOND: pure and mixed second) derivatives and, with
+// ADV / KO, shift advection and dissipation.
+template <class B, bool SECOND, bool ADV, bool KO>
 __device__ __forceinline__ void lds_derivs(const double* c, const DevParams& P, const double beta[3], FieldDerivs& r) {
+  Lines l;
+  Cross x, y;
+  lines_load<B>(c, l);
+  if constexpr (SECOND) cross_load<B>(c, 0, 1, x);
+  fence();
   double acc = 0.0;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    double v[7];
-    lds_line<B>(c, a, v);
     double d2 = 0.0;
-    op_line<SECOND, ADV, KO>(v, beta[a], P.i12h[a], P.i12h2[a], P.i24h[a], P.iko[a], r.d1[a], d2, acc);
+    op_line<SECOND, ADV, KO>(l.v[a], beta[a], P.i12h[a], P.i12h2[a], P.i24h[a], P.iko[a], r.d1[a], d2, acc);
     if (SECOND) r.d2[S(a, a)] = d2;
   }
   r.advko = acc;
-  if (SECOND) {
-    r.d2[S(0, 1)] = lds_mixed<B>(c, 0, 1, P.i144[0]);
-    r.d2[S(0, 2)] = lds_mixed<B>(c, 0, 2, P.i144[1]);
-    r.d2[S(1, 2)] = lds_mixed<B>(c, 1, 2, P.i144[2]);
+  if constexpr (SECOND) {
+    cross_load<B>(c, 0, 2, y);
+    fence();
+    r.d2[S(0, 1)] = cross_value(x, P.i144[0]);
+    cross_load<B>(c, 1, 2, x);
+    fence();
+    r.d2[S(0, 2)] = cross_value(y, P.i144[1]);
+    r.d2[S(1, 2)] = cross_value(x, P.i144[2]);
   }
 }
 
@@ -145,56 +180,98 @@ __device__ __forceinline__ void wait_vm(int n) {
   }
 }
 
-// LDS-direct halo staging: each lane holds the byte offsets of its pair in a field (one per
-// round); a fetch issues NR loads that write the field's halo box straight into an LDS buffer,
-// round q of wave w filling pairs [256 q + 64 w, 256 q + 64 w + 64). No registers hold the data.
+// LDS-direct halo staging: each lane loads one pair of x-neighbours per round, straight into an LDS
+// buffer (round q of wave w fills pairs [256 q + 64 w, 256 q + 64 w + 64)); no registers hold the data.
+// Which box points a lane loads is fixed, in box coordinates: box points that no stencil reads stand
+// for a point of a cache line the brick reads anyway, so that only the lines the stencils use are
+// requested, with two sets of them. Fields with second derivatives read x-halo points in rows within
+// +-2 of the brick in y and z with the other coordinate inside (mixed xy and xz derivatives; +-3 axial
+// ones in rows inside in both), the other rows only over the brick's x-range (y and z stencils, mixed
+// yz ones within +-2 in both), and the box's corner rows not at all. Fields with first derivatives
+// only read the x-halo in rows inside in y and z, the brick's x-range in rows inside in one of them.
+// The coordinates are packed five bits each, both sets in one word per round, formed once per launch,
+// so a brick costs a few multiply-adds per offset, plus the periodic wrap only where its box crosses
+// the grid's faces.
+//
+// A pair must not straddle the seam between x = n0 - 1 and x = 0. With n0 even the box starts at the
+// even i0 - 4 and no pair does. With n0 odd the seam at the upper face falls inside a pair there, so a
+// box that reaches it starts one point later (shift 1; its stencils need no more than i0 - 3). One seam
+// per box is assumed: n0 >= BX + 5, for the widest brick 21 (halo_fits). Pairs are 8-byte aligned only, then and for any base
+// address, which the LDS-direct loads take (checked on the device at every offset).
+constexpr bool halo_fits(int n0) { return n0 % 2 == 0 || n0 >= 21; }
 template <class B>
 struct HaloDma {
-  uint32_t goffb[B::NOFF];
-  __device__ __forceinline__ void init(int i0, int j0, int k0, const int n[3]) { offsets(i0, j0, k0, n, goffb); }
-  // Box points that no stencil reads load a pair from a cache line the brick reads anyway, so
-  // that only the lines the stencils use are requested. Offsets [0, NR): fields with second
-  // derivatives -- x-halo reads come from rows within +-2 of the brick in y and z with the other
-  // coordinate inside (mixed xy and xz derivatives; +-3 axial ones in rows inside in both), the
-  // other rows are read only at the brick's x-range (y and z stencils, mixed yz ones within
-  // +-2 in both), and the box's corner rows not at all. Offsets [NR, 2 NR): fields with first
-  // derivatives only -- axial stencils: the x-halo in rows inside in y and z, the brick's
-  // x-range in rows inside in one of them, nothing elsewhere.
-  static __device__ __forceinline__ void offsets(int i0, int j0, int k0, const int n[3], uint32_t goffb[B::NOFF]) {
+  static_assert(B::HX <= 32 && B::HY <= 32 && B::HZ <= 32, "five bits a coordinate");
+  uint32_t box[B::NR];    // second-derivative set in the low half, first-derivative set in the high half
+  uint32_t off[B::NOFF];  // byte offsets in a field: [0, NR) the first set, [NR, 2 NR) the second
+  static __device__ __forceinline__ int shift(int i0, int n0) { return (n0 & 1) && i0 - 4 + B::HX > n0 ? 1 : 0; }
+  __device__ __forceinline__ void init(int n0) {
+    const int first = n0 & 1 ? 1 : 2;  // pairs [first, NPR - 3] cover the brick's x-range (with either shift)
 #pragma unroll
     for (int q = 0; q < B::NR; ++q) {
-      const int m = threadIdx.x + 256 * q;
-      const int mm = m < B::NPAIR ? m : 0;  // padding lanes load an in-box pair into the padding
-      const int hx2 = mm % B::NPR, dy = (mm / B::NPR) % B::HY - 3, dz = mm / (B::NPR * B::HY) - 3;
+      const int e = (threadIdx.x & 255) + 256 * q;
+      const int ee = e < B::NPAIR ? e : 0;  // padding lanes load an in-box pair into the padding
+      const int hx = ee % B::NPR, y = (ee / B::NPR) % B::HY, z = ee / (B::NPR * B::HY);
+      const int dy = y - 3, dz = z - 3;
       const bool yin = dy >= 0 && dy < B::Y, zin = dz >= 0 && dz < B::Z;
       const bool y2 = dy >= -2 && dy < B::Y + 2, z2 = dz >= -2 && dz < B::Z + 2;
-      const int hxi = min(max(hx2, 2), B::NPR - 3);  // the pair moved into the brick's x-range
-      const int x = wrap_halo(i0 - 4 + 2 * hx2, n[0]), xi = wrap_halo(i0 - 4 + 2 * hxi, n[0]);
-      const int y = wrap_halo(j0 + dy, n[1]), z = wrap_halo(k0 + dz, n[2]);
-      // a row that is read nowhere is replaced by the row with y moved inside the brick (read by
-      // the z stencils of both sets at the brick's x-range)
-      const int yc = wrap_halo(j0 + min(max(dy, 0), B::Y - 1), n[1]);
+      const int hi = min(max(hx, first), B::NPR - 3);  // the pair moved into the brick's x-range
+      const int yc = min(max(dy, 0), B::Y - 1) + 3;    // the row moved inside the brick in y
       const bool xh2 = (y2 && zin) || (yin && z2), row2 = yin || zin || (y2 && z2);
-      goffb[q] = 8u * (uint32_t)((xh2 ? x : xi) + n[0] * ((row2 ? y : yc) + n[1] * z));
-      // first derivatives: rows inside in y or z are read, the others replaced as above
       const bool xh1 = yin && zin, row1 = yin || zin;
-      goffb[B::NR + q] = 8u * (uint32_t)((xh1 ? x : xi) + n[0] * ((row1 ? y : yc) + n[1] * z));
+      const uint32_t second = 2 * (xh2 ? hx : hi) | (row2 ? y : yc) << 5 | z << 10;
+      const uint32_t first1 = 2 * (xh1 ? hx : hi) | (row1 ? y : yc) << 5 | z << 10;
+      box[q] = second | first1 << 16;
     }
   }
-  // one field's halo box: SECOND selects the offset set of the fields with second derivatives
-  __device__ __forceinline__ void fetch(const double* F, uint32_t nbytes, double* buf, bool second = true) const {
-    fetch_at(F, nbytes, buf, second ? goffb : goffb + B::NR);
+  // x in [-n, 3n) to its place in [0, n): the unsigned minimum keeps x - n only where it is not negative
+  static __device__ __forceinline__ int wrap(int x, int n) {
+    uint32_t u = (uint32_t)(x + n);
+    u = min(u, u - (uint32_t)n);
+    u = min(u, u - (uint32_t)n);
+    u = min(u, u - (uint32_t)n);
+    return (int)u;
   }
-  static __device__ __forceinline__ void fetch_at(const double* F, uint32_t nbytes, double* buf,
-                                                  const uint32_t off[B::NR]) {
+  __device__ __forceinline__ void locate(int i0, int j0, int k0, const int n[3]) {
+    // opaque per brick: the unpacked coordinates are formed here, not kept (and spilled) across bricks
+#pragma unroll
+    for (int q = 0; q < B::NR; ++q) asm volatile("" : "+v"(box[q]));
+    const int x0 = i0 - 4 + shift(i0, n[0]), y0 = j0 - 3, z0 = k0 - 3;
+    if (x0 >= 0 && x0 + B::HX <= n[0] && y0 >= 0 && y0 + B::HY <= n[1] && z0 >= 0 && z0 + B::HZ <= n[2]) {  // uniform
+      const uint32_t base = (uint32_t)(x0 + n[0] * (y0 + n[1] * z0));
+#pragma unroll
+      for (int q = 0; q < B::NOFF; ++q) {
+        const uint32_t b = box[q % B::NR] >> (q < B::NR ? 0 : 16);
+        off[q] = 8u * (base + (b & 31) + (uint32_t)n[0] * (((b >> 5) & 31) + (uint32_t)n[1] * ((b >> 10) & 31)));
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < B::NOFF; ++q) {
+        const uint32_t b = box[q % B::NR] >> (q < B::NR ? 0 : 16);
+        const int x = wrap(x0 + (int)(b & 31), n[0]), y = wrap(y0 + (int)((b >> 5) & 31), n[1]);
+        const int z = wrap(z0 + (int)((b >> 10) & 31), n[2]);
+        off[q] = 8u * (uint32_t)(x + n[0] * (y + n[1] * z));
+      }
+    }
+  }
+  // one field's halo box by four waves: SECOND selects the set of the fields with second derivatives
+  __device__ __forceinline__ void fetch(const double* F, uint32_t nbytes, double* buf, bool second = true) const {
     const __amdgpu_buffer_rsrc_t r = field_rsrc(F, nbytes);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
     for (int q = 0; q < B::NR; ++q)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          r, (__attribute__((address_space(3))) void*)(buf + 2 * (256 * q + 64 * w)), 16, off[q], 0, 0, 0);
+          r, (__attribute__((address_space(3))) void*)(buf + 2 * (256 * q + 64 * w)), 16, off[second ? q : B::NR + q], 0, 0, 0);
   }
 };
+
+// the thread's point in the brick's halo boxes
+template <class B>
+__device__ __forceinline__ int box_index(int i0, int n0) {
+  const int pt = threadIdx.x & 255;
+  return (pt % B::X + B::XO - HaloDma<B>::shift(i0, n0)) +
+         B::SY * (((pt / B::X) % B::Y + 3) + B::HY * (pt / (B::X * B::Y) + 3));
+}
 
 // ---------------------------------------------------------------- the two roles of the stage kernel
 constexpr int kPairThreads = 512;  // waves 0-3: curvature waves, waves 4-7: transport waves, one point per thread of each
@@ -249,67 +326,6 @@ struct PairRing {
   }
 };
 
-// The halo-box points a lane of the curvature waves loads, in box coordinates, and their byte offsets
-// in a field for a given brick. Box points no stencil reads stand for a point of a line that is read
-// anyway (the two offset sets of HaloDma::offsets, whose selection this repeats in box coordinates),
-// packed five bits a coordinate, both sets in one word per load round: formed once per launch, so
-// that a brick costs a few multiply-adds per offset, plus the periodic wrap only where its box
-// crosses the grid's faces.
-template <class B>
-struct PairHalo {
-  static_assert(B::HX <= 32 && B::HY <= 32 && B::HZ <= 32, "five bits a coordinate");
-  uint32_t box[B::NR];      // second-derivative set in the low half, first-derivative set in the high half
-  uint32_t off[B::NOFF];    // byte offsets: [0, NR) the first set, [NR, 2 NR) the second
-  __device__ __forceinline__ void init() {
-#pragma unroll
-    for (int q = 0; q < B::NR; ++q) {
-      const int e = threadIdx.x + 256 * q;
-      const int ee = e < B::NPAIR ? e : 0;  // padding lanes load an in-box pair into the padding
-      const int hx = ee % B::NPR, y = (ee / B::NPR) % B::HY, z = ee / (B::NPR * B::HY);
-      const int dy = y - 3, dz = z - 3;
-      const bool yin = dy >= 0 && dy < B::Y, zin = dz >= 0 && dz < B::Z;
-      const bool y2 = dy >= -2 && dy < B::Y + 2, z2 = dz >= -2 && dz < B::Z + 2;
-      const int hi = min(max(hx, 2), B::NPR - 3);        // the pair moved into the brick's x-range
-      const int yc = min(max(dy, 0), B::Y - 1) + 3;      // the row moved inside the brick in y
-      const bool xh2 = (y2 && zin) || (yin && z2), row2 = yin || zin || (y2 && z2);
-      const bool xh1 = yin && zin, row1 = yin || zin;
-      const uint32_t lo = 2 * (xh2 ? hx : hi) | (row2 ? y : yc) << 5 | z << 10;
-      const uint32_t hi16 = 2 * (xh1 ? hx : hi) | (row1 ? y : yc) << 5 | z << 10;
-      box[q] = lo | hi16 << 16;
-    }
-  }
-  // x in [-n, 3n) to its place in [0, n): the unsigned minimum keeps x - n only where it is not negative
-  static __device__ __forceinline__ int wrap(int x, int n) {
-    uint32_t u = (uint32_t)(x + n);
-    u = min(u, u - (uint32_t)n);
-    u = min(u, u - (uint32_t)n);
-    u = min(u, u - (uint32_t)n);
-    return (int)u;
-  }
-  __device__ __forceinline__ void locate(int i0, int j0, int k0, const int n[3]) {
-    // opaque per brick: the unpacked coordinates are formed here, not kept (and spilled) across bricks
-#pragma unroll
-    for (int q = 0; q < B::NR; ++q) asm volatile("" : "+v"(box[q]));
-    const int x0 = i0 - 4, y0 = j0 - 3, z0 = k0 - 3;
-    if (x0 >= 0 && x0 + B::HX <= n[0] && y0 >= 0 && y0 + B::HY <= n[1] && z0 >= 0 && z0 + B::HZ <= n[2]) {  // uniform
-      const uint32_t base = (uint32_t)(x0 + n[0] * (y0 + n[1] * z0));
-#pragma unroll
-      for (int q = 0; q < B::NOFF; ++q) {
-        const uint32_t b = box[q % B::NR] >> (q < B::NR ? 0 : 16);
-        off[q] = 8u * (base + (b & 31) + (uint32_t)n[0] * (((b >> 5) & 31) + (uint32_t)n[1] * ((b >> 10) & 31)));
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < B::NOFF; ++q) {
-        const uint32_t b = box[q % B::NR] >> (q < B::NR ? 0 : 16);
-        const int x = wrap(x0 + (int)(b & 31), n[0]), y = wrap(y0 + (int)((b >> 5) & 31), n[1]);
-        const int z = wrap(z0 + (int)((b >> 10) & 31), n[2]);
-        off[q] = 8u * (uint32_t)(x + n[0] * (y + n[1] * z));
-      }
-    }
-  }
-};
-
 // What a stage does for one brick, uniform over the workgroup: the arrays and field size of its
 // grid, the stage's time and RK4 weights, and the brick's origin.
 struct StageItem {
@@ -327,11 +343,6 @@ __device__ __forceinline__ int pair_point(const StageItem& m, const int n[3], bo
   const int i = m.i0 + pt % B::X, j = m.j0 + (pt / B::X) % B::Y, k = m.k0 + pt / (B::X * B::Y);
   active = i < n[0] && j < n[1] && k < n[2];
   return active ? i + n[0] * (j + n[1] * k) : 0;
-}
-template <class B>
-__device__ __forceinline__ int pair_cidx() {
-  const int pt = threadIdx.x & 255;
-  return (pt % B::X + B::XO) + B::SY * (((pt / B::X) % B::Y + 3) + B::HY * (pt / (B::X * B::Y) + 3));
 }
 template <class B>
 __device__ __forceinline__ void flux_neighbours(const StageItem& m, const int n[3], int c, uint32_t fo[3][4]) {
@@ -377,46 +388,6 @@ __device__ __forceinline__ void pin(double& x) { asm volatile("" : "+v"(x)); }
 template <int I>
 using iv = std::integral_constant<int, I>;
 
-// Stencil taps of one field in registers. The roles load taps one batch ahead of the arithmetic that
-// uses them, with a scheduling fence after every batch: left to itself the compiler reads two or
-// three taps at a time and waits for each, about 25 LDS latencies per interval.
-__device__ __forceinline__ void fence() { __builtin_amdgcn_sched_barrier(0); }
-struct Lines {  // offsets -3..+3 along each axis (only the used ones are loaded)
-  double v[3][7];
-};
-template <class B>
-__device__ __forceinline__ void lines_load(const double* c, Lines& l) {
-#pragma unroll
-  for (int a = 0; a < 3; ++a) lds_line<B>(c, a, l.v[a]);
-}
-struct Cross {  // the 16 taps of a mixed derivative, [offset along a][offset along b] of -2, -1, 1, 2
-  double v[4][4];
-};
-template <class B>
-__device__ __forceinline__ void cross_load(const double* c, int a, int b, Cross& x) {
-  const int sa = a == 0 ? 1 : (a == 1 ? B::SY : B::SZ);
-  const int sb = b == 0 ? 1 : (b == 1 ? B::SY : B::SZ);
-  const int o[4] = {-2, -1, 1, 2};
-#pragma unroll
-  for (int p = 0; p < 4; ++p)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) x.v[p][q] = c[o[p] * sa + o[q] * sb];
-}
-__device__ __forceinline__ double cross_value(const Cross& x, double i144) {
-  double in[4];
-#pragma unroll
-  for (int p = 0; p < 4; ++p) in[p] = (x.v[p][0] - x.v[p][3]) + 8.0 * (x.v[p][2] - x.v[p][1]);
-  return ((in[0] - in[3]) + 8.0 * (in[2] - in[1])) * i144;
-}
-// First and (SECOND) pure second derivatives from the lines.
-template <bool SECOND>
-__device__ __forceinline__ void lines_derivs(const Lines& l, const DevParams& P, FieldDerivs& r) {
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    double none = 0.0;
-    op_line<SECOND, false, false>(l.v[a], 0.0, P.i12h[a], P.i12h2[a], 0.0, 0.0, r.d1[a], SECOND ? r.d2[S(a, a)] : none, none);
-  }
-}
 // The derivatives of an interval's two fields, K0 and K1 = 0 (not differentiated), 1 (first) or 2
 // (first and second): use0 / use1 take each as soon as it is there; between() runs while the first
 // taps arrive.
@@ -503,8 +474,7 @@ template <class B, int SC, class Seq>
 __device__ __forceinline__ void curvature_waves(Seq& seq, double* smem) {
   using R = PairRing<B>;
   double* ex = smem + 6 * R::PB + threadIdx.x;
-  const int cidx = pair_cidx<B>();
-  PairHalo<B> halo;
+  HaloDma<B> halo;
   StageItem m;
   if (!seq.first(m)) return;  // uniform; the transport waves leave too
   double gi[6];
@@ -545,7 +515,7 @@ __device__ __forceinline__ void curvature_waves(Seq& seq, double* smem) {
   };
   int slot = 0;
   point_load(m, seq.P().n);
-  halo.init();
+  halo.init(seq.P().n[0]);
   halo.locate(m.i0, m.j0, m.k0, seq.P().n);
   issue(iv<0>(), m, 0);
   issue(iv<1>(), m, 1);
@@ -554,6 +524,7 @@ __device__ __forceinline__ void curvature_waves(Seq& seq, double* smem) {
   lds_barrier();
   for (;;) {
     const DevParams P = seq.P();
+    const int cidx = box_index<B>(m.i0, P.n[0]);
     StageItem nx;
     const double* cur;  // halo box of the interval's first field, at the thread's point
     auto begin = [&](auto I) {
@@ -769,7 +740,6 @@ __device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
   using Pre = typename Sink::Pre;
   const double* ex = smem + 6 * R::PB + (threadIdx.x & 255);
   double* nvals = smem + R::LDS + (threadIdx.x & 255);  // the sink's parked values
-  const int cidx = pair_cidx<B>();
   StageItem m;
   if (!seq.first(m)) return;  // uniform; the curvature waves leave too
   double cen[NF];
@@ -785,6 +755,7 @@ __device__ __forceinline__ void transport_waves(Seq& seq, double* smem) {
   lds_barrier();
   for (;;) {
     const DevParams P = seq.P();
+    const int cidx = box_index<B>(m.i0, P.n[0]);
     Sink sink(m, c, active, P.alpha_collapse, nvals);
     const double* cur;
     auto end = [&](auto) {

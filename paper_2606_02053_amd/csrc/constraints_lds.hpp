@@ -89,9 +89,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const uint32_t nbytes = (uint32_t)(fs * 8);
   const int t = threadIdx.x;
   const int tx = t % 16, ty = (t / 16) % 4, tz = t / 64;
-  const int cidx = (tx + ConsBrick::XO) + ConsBrick::SY * ((ty + 3) + ConsBrick::HY * (tz + 3));
   Red mine = red_neutral();
   HaloDma<ConsBrick> hc;
+  hc.init(P.n[0]);
   // T.order 2: round w of the XCD-blocked order; else brick slot w of the slab or linear order
   const bool blocked = T.order == 2;
   const int nslots = blocked ? T.ngroups : (T.xcd_order ? 8 * T.per : T.nbricks);
@@ -109,8 +109,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int i = i0 + tx, j = j0 + ty, k = k0 + tz;
     const bool active = i < P.n[0] && j < P.n[1] && k < P.n[2];
     const int p = active ? i + P.n[0] * (j + P.n[1] * k) : 0;
-    hc.init(i0, j0, k0, P.n);
-    LdsDerivs der{hc, ring, U, fs, nbytes, cidx, P, 0};
+    hc.locate(i0, j0, k0, P.n);
+    LdsDerivs der{hc, ring, U, fs, nbytes, box_index<ConsBrick>(i0, P.n[0]), P, 0};
     der.start();
     double H, M[3], Hn;
     bool bad;

@@ -70,8 +70,7 @@ struct ScLds {
 // T: 16x4x4 bricks. T.order 2: the XCD-blocked order (a persistent grid of the resident
 // workgroups; each round, an XCD's workgroups take one compact block of bricks); else with
 // T.xcd_order, slot w is brick (w mod 8) * T.per + w / 8, so each XCD walks its own slab of brick
-// layers, and the workgroups stride over the slots. Needs n0 even and U, Sc 16-byte aligned
-// (aligned pairs of x-neighbours).
+// layers, and the workgroups stride over the slots. Needs halo_fits(n0).
 template <int MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_scalar_stage_lds(
     const double* __restrict__ U, const double* __restrict__ Sc, double* __restrict__ src,
@@ -81,8 +80,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const uint32_t nbytes = (uint32_t)(fs * 8);
   const int t = threadIdx.x;
   const int tx = t % 16, ty = (t / 16) % 4, tz = t / 64;
-  const int cidx = (tx + ScBrick::XO) + ScBrick::SY * ((ty + 3) + ScBrick::HY * (tz + 3));
   HaloDma<ScBrick> hc;
+  hc.init(P.n[0]);
   const bool blocked = T.order == 2;
   const int nslots = blocked ? T.ngroups : (T.xcd_order ? 8 * T.per : T.nbricks);
   const int first = blocked ? 0 : (int)blockIdx.x, stride = blocked ? 1 : (int)gridDim.x;
@@ -99,8 +98,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int i = i0 + tx, j = j0 + ty, k = k0 + tz;
     const bool active = i < P.n[0] && j < P.n[1] && k < P.n[2];
     const int p = active ? i + P.n[0] * (j + P.n[1] * k) : 0;  // inactive threads evaluate point 0
-    hc.init(i0, j0, k0, P.n);
-    ScLds der{hc, ring, U, Sc, fs, nbytes, cidx, P, 0};
+    hc.locate(i0, j0, k0, P.n);
+    ScLds der{hc, ring, U, Sc, fs, nbytes, box_index<ScBrick>(i0, P.n[0]), P, 0};
     der.start();
     scalar_stage_point<MODE>(U, Sc, src, sun, sacc, sout, fs, P, p, active, der, ca, cn);
   }

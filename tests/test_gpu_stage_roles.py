@@ -53,3 +53,37 @@ def test_many_bricks_per_workgroup_and_failure_counts(P, orc, n, order):
         count[variant] = sol.status()["prim_fail"]
     assert err_fields(out[0], out[1])[0] < 1e-13
     assert count[0] == count[1] == 37
+
+
+@pytest.mark.parametrize("n", [(19, 9, 8), (21, 8, 9), (33, 9, 8), (35, 10, 11), (49, 8, 8)])
+def test_odd_widths(P, orc, n):
+    """Odd n0: the narrowest LDS-staged width (21) and the widest direct one (19), and widths whose last
+    brick holds 1, 3 and 5 columns, so that the upper face cuts the halo boxes of two bricks; state
+    arrays at either 8-byte alignment give the same bits."""
+    L = tuple(0.25 * m for m in n)
+    s, sol = mk(P, orc, n, L)
+    u = fuzz_state(n, seed=33)
+    sol.set_state(to_dev(u), t=0.2)
+    ref, _ = orc.rhs(s, u, t=0.2)
+    got = sol.rhs()
+    assert err_fields(got.cpu().numpy(), ref)[0] < 1e-11
+    buf = torch.empty(u.size + 1, dtype=torch.float64, device="cuda")
+    for k in (0, 1):
+        view = buf[k:k + u.size]
+        view.copy_(sol.u.reshape(-1))
+        out = torch.empty_like(sol.u)
+        P.cosmos_rhs(sol.grid, sol.params, 0.2, view, out, sol.ws)
+        assert torch.equal(out, got), k
+    fields = {}
+    for variant in (0, 1):
+        sol.params.variant = variant
+        _, H, M = sol.constraints(want_fields=True)
+        fields[variant] = torch.cat([H.reshape(-1), M.reshape(-1)])
+    assert torch.equal(fields[0], fields[1])
+    kb = fuzz_state(n, seed=34)
+    ws = torch.empty(P.cosmos_adjoint_workspace_bytes(sol.grid), dtype=torch.uint8, device="cuda")
+    vjp = torch.empty_like(sol.u)
+    P.cosmos_rhs_vjp(sol.grid, sol.params, 0.2, sol.u, to_dev(kb), vjp, ws)
+    tape = orc.vjp(s, u, kb, "rhs", t=0.2).reshape(25, -1)
+    d = np.abs(vjp.cpu().numpy().reshape(25, -1) - tape).max(axis=1)
+    assert (d / np.maximum(np.abs(tape).max(axis=1), 1e-8 * np.abs(tape).max())).max() < 1e-11
