@@ -94,6 +94,86 @@ __device__ __forceinline__ double cross_value(const Cross& x, double i144) {
   for (int p = 0; p < 4; ++p) in[p] = (x.v[p][0] - x.v[p][3]) + 8.0 * (x.v[p][2] - x.v[p][1]);
   return ((in[0] - in[3]) + 8.0 * (in[2] - in[1])) * i144;
 }
+// Mixed derivatives without the 16 taps each, on bricks whose x-rows are the wave's rows of 16 lanes:
+// the inner first difference (along y for xy, along z for xz and yz) at the four neighbours of the
+// outer one is what other lanes of the wave hold already. Only the columns x = -2, -1, 16, 17 (xy, xz)
+// and, on 16 x 4 bricks, the rows y = -2, -1, 4, 5 (yz) lie outside the wave: 4 taps a lane instead of
+// 16. The batches of fields with second derivatives are bound by the LDS reads (111-116 B/clk per CU):
+// 61 -> 25 values a point, stage kernel at 256^3 5.84 -> 5.64 ms, 96^3 308 -> 299 us, 32^3
+// 21.6 -> 20.2 us, constraints at 128^3 485 -> 440 us a call. Same operations on the same values as cross_value, so the same bits. Every lane of
+// the wave must be active; brick points beyond the grid take part with their staged (wrapped) values.
+struct Edge {
+  double v[4];  // taps -2, -1, 1, 2 of the inner difference at the lane's outside column or row
+};
+// Lanes 0, 1, 14, 15 of a row stand for the columns -2, -1, 16, 17; the other lanes' taps are not used.
+template <class B>
+__device__ __forceinline__ void columns_load(const double* c, int b, Edge& e) {
+  const int sb = b == 1 ? B::SY : B::SZ;
+  const double* o = c + ((threadIdx.x & 15) < 8 ? -2 : 2);
+  const int t[4] = {-2, -1, 1, 2};
+#pragma unroll
+  for (int q = 0; q < 4; ++q) e.v[q] = o[t[q] * sb];
+}
+// Lane rows 0, 1, 2, 3 stand for y = -2, -1, 4, 5.
+template <class B>
+__device__ __forceinline__ void rows_load(const double* c, Edge& e) {
+  const double* o = c + ((threadIdx.x & 32) ? 2 : -2) * B::SY;
+  const int t[4] = {-2, -1, 1, 2};
+#pragma unroll
+  for (int q = 0; q < 4; ++q) e.v[q] = o[t[q] * B::SZ];
+}
+// x of the lane that the lane shift CTRL selects in the same row of 16, or `edge` where it has none
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double x, double edge) {
+  const long long a = __double_as_longlong(x), e = __double_as_longlong(edge);
+  const int lo = __builtin_amdgcn_update_dpp((int)e, (int)a, CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp((int)(e >> 32), (int)(a >> 32), CTRL, 0xf, 0xf, false);
+  return __longlong_as_double((long long)(unsigned)lo | (long long)hi << 32);
+}
+// rows (a0 a1 a2 a3), (b0 b1 b2 b3) -> (a0 a1 b0 b1), (a2 a3 b2 b3)
+__device__ __forceinline__ void swap_halves(double& a, double& b) {
+  const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  a = __longlong_as_double((long long)((unsigned long long)hi[0] << 32 | lo[0]));
+  b = __longlong_as_double((long long)((unsigned long long)hi[1] << 32 | lo[1]));
+}
+// rows (a0 a1 a2 a3), (b0 b1 b2 b3) -> (a0 b0 a2 b2), (a1 b1 a3 b3)
+__device__ __forceinline__ void swap_rows(double& a, double& b) {
+  const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  a = __longlong_as_double((long long)((unsigned long long)hi[0] << 32 | lo[0]));
+  b = __longlong_as_double((long long)((unsigned long long)hi[1] << 32 | lo[1]));
+}
+// the inner difference: v is the point's own line along the inner axis
+__device__ __forceinline__ double inner_own(const double v[7]) { return (v[1] - v[5]) + 8.0 * (v[4] - v[2]); }
+__device__ __forceinline__ double inner_edge(const Edge& e) { return (e.v[0] - e.v[3]) + 8.0 * (e.v[2] - e.v[1]); }
+__device__ __forceinline__ double columns_value(const double v[7], const Edge& e, double i144) {
+  const double own = inner_own(v), two = inner_edge(e);
+  const double one = lane_shift<0xB1>(two, two);  // neighbouring lanes swapped: columns -1, 16 in lanes 0, 15
+  const double m2 = lane_shift<0x112>(own, two), m1 = lane_shift<0x111>(own, one);  // from lanes - 2, - 1
+  const double p1 = lane_shift<0x101>(own, one), p2 = lane_shift<0x102>(own, two);  // from lanes + 1, + 2
+  return ((m2 - p2) + 8.0 * (p1 - m1)) * i144;
+}
+__device__ __forceinline__ double rows_value(const double v[7], const Edge& e, double i144) {
+  const double own = inner_own(v), out = inner_edge(e);  // rows o0 o1 o2 o3; e0 e1 e2 e3
+  double m2 = out, s = own, r = own, p2 = out;
+  swap_halves(m2, s);                                    // m2 = e0 e1 o0 o1
+  swap_halves(r, p2);                                    // p2 = o2 o3 e2 e3
+  double m1 = own, p1 = own;
+  swap_rows(m1, p1);                                     // o0 o0 o2 o2; o1 o1 o3 o3
+  double a = m2, b = p2;
+  swap_rows(a, m1);                                      // m1 = e1 o0 o1 o2
+  swap_rows(p1, b);                                      // p1 = o1 o2 o3 e2
+  return ((m2 - p2) + 8.0 * (p1 - m1)) * i144;
+}
+// Which mixed derivatives of a brick are formed so; the others take cross_load's 16 taps.
+template <class B>
+constexpr bool kByColumns = B::X == 16;
+template <class B>
+constexpr bool kByRows = B::X == 16 && B::Y == 4;
+
 // First and (SECOND) pure second derivatives from the lines.
 template <bool SECOND>
 __device__ __forceinline__ void lines_derivs(const Lines& l, const DevParams& P, FieldDerivs& r) {
@@ -107,10 +187,15 @@ __device__ __forceinline__ void lines_derivs(const Lines& l, const DevParams& P,
 // ADV / KO, shift advection and dissipation.
 template <class B, bool SECOND, bool ADV, bool KO>
 __device__ __forceinline__ void lds_derivs(const double* c, const DevParams& P, const double beta[3], FieldDerivs& r) {
+  static_assert(!SECOND || kByRows<B>, "16 x 4 bricks");
   Lines l;
-  Cross x, y;
+  Edge e1, e2, e3;
   lines_load<B>(c, l);
-  if constexpr (SECOND) cross_load<B>(c, 0, 1, x);
+  if constexpr (SECOND) {
+    columns_load<B>(c, 1, e1);
+    columns_load<B>(c, 2, e2);
+    rows_load<B>(c, e3);
+  }
   fence();
   double acc = 0.0;
 #pragma unroll
@@ -121,13 +206,9 @@ __device__ __forceinline__ void lds_derivs(const double* c, const DevParams& P, 
   }
   r.advko = acc;
   if constexpr (SECOND) {
-    cross_load<B>(c, 0, 2, y);
-    fence();
-    r.d2[S(0, 1)] = cross_value(x, P.i144[0]);
-    cross_load<B>(c, 1, 2, x);
-    fence();
-    r.d2[S(0, 2)] = cross_value(y, P.i144[1]);
-    r.d2[S(1, 2)] = cross_value(x, P.i144[2]);
+    r.d2[S(0, 1)] = columns_value(l.v[1], e1, P.i144[0]);
+    r.d2[S(0, 2)] = columns_value(l.v[2], e2, P.i144[1]);
+    r.d2[S(1, 2)] = rows_value(l.v[2], e3, P.i144[2]);
   }
 }
 
@@ -394,44 +475,61 @@ using iv = std::integral_constant<int, I>;
 template <class B, int K0, int K1, class Between, class Use0, class Use1>
 __device__ __forceinline__ void pair_derivs(const double* c0, const double* c1, const DevParams& P, Between between,
                                             Use0 use0, Use1 use1) {
+  constexpr bool columns = kByColumns<B>, rows = kByRows<B>;
   Lines l;
+  Edge e1, e2, e3;
   Cross x, y;
-  FieldDerivs d;
-  lines_load<B>(c0, l);
-  if constexpr (K0 == 2) cross_load<B>(c0, 0, 1, x);
+  FieldDerivs d, e;
+  auto load_first = [&](const double* c) {
+    lines_load<B>(c, l);
+    if constexpr (columns) {
+      columns_load<B>(c, 1, e1);
+      columns_load<B>(c, 2, e2);
+    }
+    if constexpr (rows) rows_load<B>(c, e3);
+  };
+  auto mixed = [&](const double* c, FieldDerivs& r) {  // the taps of the yz derivative follow into x
+    if constexpr (columns) {
+      if constexpr (!rows) {
+        cross_load<B>(c, 1, 2, x);
+        fence();
+      }
+      r.d2[S(0, 1)] = columns_value(l.v[1], e1, P.i144[0]);
+      r.d2[S(0, 2)] = columns_value(l.v[2], e2, P.i144[1]);
+      if constexpr (rows) r.d2[S(1, 2)] = rows_value(l.v[2], e3, P.i144[2]);
+    } else {
+      cross_load<B>(c, 0, 1, x);
+      cross_load<B>(c, 0, 2, y);
+      fence();
+      r.d2[S(0, 1)] = cross_value(x, P.i144[0]);
+      cross_load<B>(c, 1, 2, x);
+      fence();
+      r.d2[S(0, 2)] = cross_value(y, P.i144[1]);
+    }
+  };
+  if constexpr (K0 == 2)
+    load_first(c0);
+  else
+    lines_load<B>(c0, l);
   fence();
   between();
   fence();
   lines_derivs<K0 == 2>(l, P, d);
-  if constexpr (K0 == 2) {
-    cross_load<B>(c0, 0, 2, y);
-    fence();
-    d.d2[S(0, 1)] = cross_value(x, P.i144[0]);
-    cross_load<B>(c0, 1, 2, x);
-    fence();
-    d.d2[S(0, 2)] = cross_value(y, P.i144[1]);
-    if constexpr (K1 != 0) lines_load<B>(c1, l);
-    fence();
-    d.d2[S(1, 2)] = cross_value(x, P.i144[2]);
-    if constexpr (K1 == 2) cross_load<B>(c1, 0, 1, x);
-    fence();
-  } else if constexpr (K1 != 0) {
+  if constexpr (K0 == 2) mixed(c0, d);
+  // the second field's lines are on their way while the first one's last derivative is formed and used
+  if constexpr (K1 == 2)
+    load_first(c1);
+  else if constexpr (K1 == 1)
     lines_load<B>(c1, l);
-    fence();
-  }
+  fence();
+  if constexpr (K0 == 2 && !rows) d.d2[S(1, 2)] = cross_value(x, P.i144[2]);
   use0(d);
   if constexpr (K1 != 0) {
     fence();
-    FieldDerivs e;
     lines_derivs<K1 == 2>(l, P, e);
     if constexpr (K1 == 2) {
-      cross_load<B>(c1, 0, 2, y);
-      fence();
-      e.d2[S(0, 1)] = cross_value(x, P.i144[0]);
-      cross_load<B>(c1, 1, 2, x);
-      fence();
-      e.d2[S(0, 2)] = cross_value(y, P.i144[1]);
-      e.d2[S(1, 2)] = cross_value(x, P.i144[2]);
+      mixed(c1, e);
+      if constexpr (!rows) e.d2[S(1, 2)] = cross_value(x, P.i144[2]);
     }
     use1(e);
   }
