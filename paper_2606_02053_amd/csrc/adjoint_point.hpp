@@ -235,7 +235,7 @@ __host__ __device__ inline void flux_reverse(double w, int a, const FluxIn& in, 
 template <class Src, class Sink>
 __host__ __device__ inline void pt_vjp(const DevParams& P, double t, const Src& src, Sink& out) {
   const double third = 1.0 / 3.0;
-  const double chi = src.val(F_CHI), alpha = src.val(F_ALP);
+  double chi = src.val(F_CHI), alpha = src.val(F_ALP);
   double gt[6], gi[6];
 #pragma unroll
   for (int s = 0; s < 6; ++s) gt[s] = src.val(F_GT + s);
@@ -330,6 +330,22 @@ __host__ __device__ inline void pt_vjp(const DevParams& P, double t, const Src& 
   }
   src.fence();
 
+  // The point values opaque from here on: what was formed from them (the inverse metric's minors,
+  // quotients by chi, products with X_ij's cotangent) is formed again where it is used, not kept in
+  // registers across the sweep. With this and the accumulators pinned between the sections (the
+  // compiler moves sums towards their last use otherwise, and their terms stay live), the 196
+  // registers the staged kernel spilled and the 178 of the direct one are none.
+  auto hide = [&]() {
+    src.pin(chi);
+    src.pin(alpha);
+#pragma unroll
+    for (int s = 0; s < 6; ++s) {
+      src.pin(gt[s]);
+      src.pin(gi[s]);
+      src.pin(X6b[s]);
+    }
+  };
+  hide();
   // ---- first differences of chi, alpha, beta; the conformal-factor terms of the Hessians
   double dchi[3], dal[3], db[3][3], DDchi[6], DDa[6];  // DDchi, DDa: second differences for now
   src.d12(F_CHI, dchi, DDchi);
@@ -385,6 +401,7 @@ __host__ __device__ inline void pt_vjp(const DevParams& P, double t, const Src& 
   src.fence();
 
   // ---- connection and its reverse
+  hide();
   double Gl[3][6], sg[3], SjkbD[6];  // SjkbD: the d gamma part of the S^jk cotangent
   {
     double dgt[6][3];
@@ -435,6 +452,15 @@ __host__ __device__ inline void pt_vjp(const DevParams& P, double t, const Src& 
       gib[s] += trDDb * wsym(s) * DDchi[s] + Cg * wsym(s) * DDa[s];
     }
   }
+#pragma unroll
+  for (int s = 0; s < 6; ++s) {
+    src.pin(Xacc[s]);
+    src.pin(bgt[s]);
+    src.pin(gib[s]);
+  }
+  src.pin(balpha);
+  src.pin(bchi);
+  src.fence();
   double Gub[3][6], Glb[3][6], Gdb[3], AupbG[6];  // AupbG: the connection part of the A^ij cotangent
   {
     double Aup[6], innb[3];
@@ -475,6 +501,17 @@ __host__ __device__ inline void pt_vjp(const DevParams& P, double t, const Src& 
       }
   }
 #pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    src.pin(bdal[k]);
+    src.pin(bdchi[k]);
+    src.pin(Gdb[k]);
+#pragma unroll
+    for (int s = 0; s < 6; ++s) src.pin(Gub[k][s]);
+  }
+#pragma unroll
+  for (int s = 0; s < 6; ++s) src.pin(AupbG[s]);
+  src.fence();
+#pragma unroll
   for (int s = 0; s < 6; ++s) {
     src.fence();
     const int i = SI(s), j = SJ(s);
@@ -510,6 +547,19 @@ __host__ __device__ inline void pt_vjp(const DevParams& P, double t, const Src& 
       }
     Xacc[s] += alpha * dr;
     balpha += X6b[s] * dr;
+    src.pin(Xacc[s]);
+    src.pin(balpha);
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+        src.pin(Gub[k][q]);
+        src.pin(Glb[k][q]);
+      }
+#pragma unroll
+    for (int q = 0; q < 6; ++q) src.pin(gib[q]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) src.pin(Gdb[q]);
   }
   src.fence();
 #pragma unroll
@@ -550,6 +600,7 @@ __host__ __device__ inline void pt_vjp(const DevParams& P, double t, const Src& 
   }
   src.fence();
 
+  hide();
   // ---- streamed: second differences of the metric, d_a Gamma^k, shift second differences, d_a K
 #pragma unroll
   for (int s = 0; s < 6; ++s) {
@@ -615,6 +666,7 @@ __host__ __device__ inline void pt_vjp(const DevParams& P, double t, const Src& 
   src.fence();
 
   // ---- terms of the point values, and the fluid
+  hide();
   const double K = src.val(F_K);
   double At[6], Amix[3][3], Aup[6];
 #pragma unroll
@@ -705,6 +757,21 @@ __host__ __device__ inline void pt_vjp(const DevParams& P, double t, const Src& 
     balpha -= 2.0 * rg * At[s];
     bAt[s] -= 2.0 * rg * alpha;
   }
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    src.pin(bAt[q]);
+    src.pin(bgt[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    src.pin(Amixb[q / 3][q % 3]);
+    src.pin(bdb[q / 3][q % 3]);
+  }
+  src.pin(balpha);
+  src.pin(bK);
+  src.pin(bchi);
+  src.pin(divbb);
+  src.fence();
   {
     const double Str = R.S2 * R.invX + 3.0 * R.P;
     const double AA = contract_sym(At, Aup);
@@ -746,6 +813,25 @@ __host__ __device__ inline void pt_vjp(const DevParams& P, double t, const Src& 
     }
     divbb += r * (2.0 / 3.0) * Gd[i];
   }
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    src.pin(gib[q]);
+    src.pin(Aupb[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    src.pin(bdb[q / 3][q % 3]);
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    src.pin(bdchi[q]);
+    src.pin(bdal[q]);
+    src.pin(B.S[q]);
+  }
+  src.pin(balpha);
+  src.pin(bchi);
+  src.pin(divbb);
+  src.fence();
   bdb[0][0] += divbb;
   bdb[1][1] += divbb;
   bdb[2][2] += divbb;
@@ -764,6 +850,20 @@ __host__ __device__ inline void pt_vjp(const DevParams& P, double t, const Src& 
     bgt[s] += Sijb * R.P * ichi;
     ichib += Sijb * R.P * gt[s];
   }
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    src.pin(bgt[q]);
+    src.pin(Xacc[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    src.pin(B.S[q]);
+  }
+  src.pin(balpha);
+  src.pin(ichib);
+  src.pin(B.P);
+  src.pin(B.invX);
+  src.fence();
   double sgtb = 0.0;
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
@@ -827,6 +927,14 @@ __host__ __device__ inline void pt_vjp(const DevParams& P, double t, const Src& 
 #pragma unroll
     for (int c = 0; c < 3; ++c) out.val(F_ST + c, bSt[c]);
   }
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    src.pin(gib[q]);
+    src.pin(bgt[q]);
+  }
+  src.pin(bchi);
+  src.pin(balpha);
+  src.fence();
   // A^ij and A^i_j back to A_ij and the inverse metric
 #pragma unroll
   for (int s = 0; s < 6; ++s) {
