@@ -22,6 +22,13 @@ struct DirectDerivs {
   size_t fs;
   const Nbr& nb;
   const DevParams& P;
+  int c;
+  __device__ __forceinline__ double val(int f) const { return ldq(U + (size_t)f * fs, c); }
+  __device__ __forceinline__ bool nonfinite() const {
+    bool bad = false;
+    for (int f = 0; f < NF; ++f) bad = bad || !isfinite(val(f));
+    return bad;
+  }
   // a value final for this field stays in a register here (as with the LDS source)
   __device__ __forceinline__ void pin(double& x) { asm volatile("" : "+v"(x)); }
   template <bool SECOND>
@@ -43,18 +50,16 @@ struct DirectDerivs {
 // between fields keeps it in a register there instead of recomputing it later from every
 // field's derivatives); it changes no value.
 template <class Der>
-__device__ __forceinline__ void constraint_point(const double* __restrict__ U, size_t fs, int c, Der& der,
-                                                 const DevParams& P, double& H, double M[3], double& Hn,
+__device__ __forceinline__ void constraint_point(size_t fs, int c, Der& der, const DevParams& P, double& H, double M[3], double& Hn,
                                                  bool& nonfinite) {
-  nonfinite = false;
-  for (int f = 0; f < NF; ++f) nonfinite = nonfinite || !isfinite(ldq(U + (size_t)f * fs, c));
+  nonfinite = der.nonfinite();
   // point values are loaded where they are needed (gt_ij twice: for its inverse, then for the
   // chi and Gt^i terms), so that they are not live across the connection
   double gi[6];
   {
     double gt[6];
 #pragma unroll
-    for (int s = 0; s < 6; ++s) gt[s] = ldq(U + (F_GT + s) * fs, c);
+    for (int s = 0; s < 6; ++s) gt[s] = der.val(F_GT + s);
     inv_sym(gt, gi);
   }
   // ---- conformal metric: second derivatives into the Ricci tensor, first into the connection
@@ -72,7 +77,7 @@ __device__ __forceinline__ void constraint_point(const double* __restrict__ U, s
   connection_and_quadratic_ricci(dgt, gi, Gu, Gd, Ric);
   double At[6];
 #pragma unroll
-  for (int s = 0; s < 6; ++s) At[s] = ldq(U + (F_AT + s) * fs, c);
+  for (int s = 0; s < 6; ++s) At[s] = der.val(F_AT + s);
   // the connection's part of M_i: -gt^jk (Gt^l_jk At_li + Gt^l_ji At_kl)
   double Mc[3];
 #pragma unroll
@@ -100,10 +105,10 @@ __device__ __forceinline__ void constraint_point(const double* __restrict__ U, s
   for (int i = 0; i < 3; ++i)
 #pragma unroll
     for (int j = 0; j < 3; ++j) AA += Amix[i][j] * Amix[j][i];
-  const double chi = ldq(U + F_CHI * fs, c);
+  const double chi = der.val(F_CHI);
   double gt[6];
 #pragma unroll
-  for (int s = 0; s < 6; ++s) gt[s] = ldq(U + (F_GT + s) * fs, c);
+  for (int s = 0; s < 6; ++s) gt[s] = der.val(F_GT + s);
   {
     FieldDerivs d;
     der.template get<true>(F_CHI, d);
@@ -129,12 +134,12 @@ __device__ __forceinline__ void constraint_point(const double* __restrict__ U, s
     }
   }
   const double R = chi * contract_sym(gi, Ric);
-  const double K = ldq(U + F_K * fs, c);
+  const double K = der.val(F_K);
   double St[3];
 #pragma unroll
-  for (int i = 0; i < 3; ++i) St[i] = ldq(U + (F_ST + i) * fs, c);
+  for (int i = 0; i < 3; ++i) St[i] = der.val(F_ST + i);
   Fluid fl;
-  recover(P.w, chi, gi, ldq(U + F_ET * fs, c), St, fl);
+  recover(P.w, chi, gi, der.val(F_ET), St, fl);
   if (P.xsrc) {  // scalar field: its energy and momentum densities join the fluid's
     fl.E += ldq(P.xsrc + SRC_E * fs, c);
 #pragma unroll
@@ -229,7 +234,7 @@ __device__ __forceinline__ void store_hm(size_t fs, int p, double H, const doubl
 }
 
 // The reduction record of one point.
-__device__ __forceinline__ Red point_record(const double* __restrict__ U, size_t fs, int p, double H, const double M[3],
+__device__ __forceinline__ Red point_record(double a, int p, double H, const double M[3],
                                             double Hn, bool bad) {
   Red mine = red_neutral();
   const double Mn = sqrt(M[0] * M[0] + M[1] * M[1] + M[2] * M[2]);
@@ -240,7 +245,6 @@ __device__ __forceinline__ Red point_record(const double* __restrict__ U, size_t
   mine.mH = (0.0 < aH) ? aH : 0.0;  // NaN never wins
   mine.mM = (0.0 < Mn) ? Mn : 0.0;
   mine.nbad = bad ? 1.0 : 0.0;
-  const double a = ldq(U + F_ALP * fs, p);
   if (a < INFINITY) {
     mine.minA = a;
     mine.arg = (double)p;
@@ -266,12 +270,12 @@ __global__ __launch_bounds__(256) void k_constraints(const double* __restrict__ 
       const int k = jk / P.n[1];
       Nbr nb;
       make_nbr(nb, i, j, k, P.n);
-      DirectDerivs der{U, fs, nb, P};
+      DirectDerivs der{U, fs, nb, P, p};
       double H, M[3], Hn;
       bool bad;
-      constraint_point(U, fs, p, der, P, H, M, Hn, bad);
+      constraint_point(fs, p, der, P, H, M, Hn, bad);
       store_hm(fs, p, H, M, Hout, Mout);
-      mine = red_combine(mine, point_record(U, fs, p, H, M, Hn, bad));
+      mine = red_combine(mine, point_record(der.val(F_ALP), p, H, M, Hn, bad));
     }
   }
   const Red r = block_tree(mine, sh);
