@@ -26,6 +26,8 @@ struct ScDirect {
   const Nbr& nb;
   const DevParams& P;
   __device__ __forceinline__ void pin(double& x) { asm volatile("" : "+v"(x)); }
+  __device__ __forceinline__ void start() {}
+  __device__ __forceinline__ void here(double&) {}
   template <bool SECOND, bool ADV, bool KO>
   __device__ __forceinline__ void get(int q, const double beta[3], FieldDerivs& d) {
     // a compiler-level fence per field: the stencil loads of later fields stay after it
@@ -51,12 +53,27 @@ __device__ __forceinline__ void scalar_stage_point(const double* __restrict__ U,
                                                    const DevParams& P, int c, bool active, Der& der, double ca,
                                                    double cn) {
   const size_t p = (size_t)c;
-  const double chi = ldq(U + F_CHI * fs, c), K = ldq(U + F_K * fs, c), alpha = ldq(U + F_ALP * fs, c);
-  double gt[6], gi[6], beta[3];
+  // the point's values and the epilogue's operands: requested before der.start(), in registers after it
+  double chi = ldq(U + F_CHI * fs, c), K = ldq(U + F_K * fs, c), alpha = ldq(U + F_ALP * fs, c);
+  double gt[6], gi[6], beta[3], Pi = ldq(Sc + fs, c);
 #pragma unroll
   for (int s = 0; s < 6; ++s) gt[s] = ldq(U + (F_GT + s) * fs, c);
 #pragma unroll
   for (int a = 0; a < 3; ++a) beta[a] = ldq(U + (F_BET + a) * fs, c);
+  double s0[2], un[2];  // by MODE: Sc or sacc; sun
+#pragma unroll
+  for (int f = 0; f < 2; ++f) {
+    s0[f] = MODE == 1 ? ldq(Sc + (size_t)f * fs, c) : (MODE >= 2 ? ldq(sacc + (size_t)f * fs, c) : 0.0);
+    un[f] = MODE == 2 ? ldq(sun + (size_t)f * fs, c) : 0.0;
+  }
+  der.start();
+  der.here(chi), der.here(K), der.here(alpha), der.here(Pi);
+#pragma unroll
+  for (int s = 0; s < 6; ++s) der.here(gt[s]);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) der.here(beta[a]);
+#pragma unroll
+  for (int f = 0; f < 2; ++f) der.here(s0[f]), der.here(un[f]);
   inv_sym(gt, gi);
   const double nob[3] = {0.0, 0.0, 0.0};
   // Contracted connection Gd^k = gt^ij Gt^k_ij = gt^kl (A_l - B_l / 2), A_l = gt^xy d_x gt_ly,
@@ -108,8 +125,6 @@ __device__ __forceinline__ void scalar_stage_point(const double* __restrict__ U,
     der.template get<false, true, true>(9, beta, d);  // upwind advection + KO of Pi
     advko_pi = d.advko;
   }
-  const double Pi = ldq(Sc + fs, c);
-
   // sources of the geometry
   double dd[6];
 #pragma unroll
@@ -147,14 +162,13 @@ __device__ __forceinline__ void scalar_stage_point(const double* __restrict__ U,
     if constexpr (MODE == 0) {
       sout[q] = r[f];
     } else if constexpr (MODE == 1) {
-      const double s0 = Sc[q];
-      sacc[q] = s0 + ca * r[f];
-      sout[q] = s0 + cn * r[f];
+      sacc[q] = s0[f] + ca * r[f];
+      sout[q] = s0[f] + cn * r[f];
     } else if constexpr (MODE == 2) {
-      sacc[q] = sacc[q] + ca * r[f];
-      sout[q] = sun[q] + cn * r[f];
+      sacc[q] = s0[f] + ca * r[f];
+      sout[q] = un[f] + cn * r[f];
     } else {
-      sout[q] = sacc[q] + ca * r[f];
+      sout[q] = s0[f] + ca * r[f];
     }
   }
 }

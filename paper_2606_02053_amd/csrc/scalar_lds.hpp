@@ -34,12 +34,16 @@ struct ScLds {
                  : (q == 6 ? U + (size_t)F_CHI * fs : (q == 7 ? U + (size_t)F_ALP * fs : Sc + (size_t)(q - 8) * fs));
   }
   // the first fields of a brick: 0 .. kScAhead - 1 issued, field 0 landed everywhere
-  __device__ __forceinline__ void start() {
+  __device__ __forceinline__ void issue() {
 #pragma unroll
     for (int q = 0; q < kScAhead; ++q) hc.fetch(field(q), nbytes, ring + q * ScBrick::NP, kScSecond[q]);
-    wait_vm((kScAhead - 1) * ScBrick::NR);
+  }
+  // (the point's loads follow the first fields', so they have landed with them)
+  __device__ __forceinline__ void start() {
+    wait_vm(0);
     lds_barrier();
   }
+  __device__ __forceinline__ void here(double& x) { pin(x); }
   // Call p (p = the field's place in the order) issues the loads of field p + 3 into the slot
   // field p - 1 used (every wave read it before the previous call's barrier), reads field p from
   // slot p % 4, then waits until field p + 1 has landed (the loads complete in issue order, so a
@@ -100,7 +104,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int p = active ? i + P.n[0] * (j + P.n[1] * k) : 0;  // inactive threads evaluate point 0
     hc.locate(i0, j0, k0, P.n);
     ScLds der{hc, ring, U, Sc, fs, nbytes, box_index<ScBrick>(i0, P.n[0]), P, 0};
-    der.start();
+    der.issue();
     scalar_stage_point<MODE>(U, Sc, src, sun, sacc, sout, fs, P, p, active, der, ca, cn);
   }
 }
