@@ -9,9 +9,12 @@
 // the largest characteristic-speed magnitude of the two interface states.
 //
 // One pre-pass kernel per stage forms the whole flux divergence: a workgroup owns
-// an 8 x 8 x 4 brick, evaluates every interface flux of the brick once into LDS
-// (9x8x4 + 8x9x4 + 8x8x5 = 896 interfaces for 256 points, in three wave-aligned
-// segments of 320) and differences them.
+// a 16 x 4 x 4 brick, evaluates every interface flux of the brick once into LDS
+// (17x4x4 + 16x5x4 + 16x4x5 = 912 interfaces for 256 points, in three wave-aligned
+// segments of 320) and differences them. About half of its time is arithmetic, half
+// the L1's work on 34 loads an interface, whose rows of 16 points are whole cache
+// lines (an 8 x 8 x 4 brick, with 896 interfaces, has twice as many rows): 96^3 99.9 ->
+// 95.6 us, 128^3 235 -> 220 us, 50x41x37 22.6 -> 19.6 us.
 // The stage kernel then reads the divergence at the point itself.
 #pragma once
 #include "bssn_device.hpp"
@@ -29,11 +32,11 @@ struct KtBrick {
   static constexpr int PX = (NX + 63) / 64 * 64, PY = (NY + 63) / 64 * 64, PZ = (NZ + 63) / 64 * 64;
   static constexpr int P = PX + PY + PZ;
 };
-constexpr int kKtBX = 8, kKtBY = 8, kKtBZ = 4;  // brick of k_fluid_kt
+constexpr int kKtBX = 16, kKtBY = 4, kKtBZ = 4;  // brick of k_fluid_kt
 using KtB = KtBrick<kKtBX, kKtBY, kKtBZ>;
 constexpr int kKtThreads = KtB::threads;
-constexpr int kKtP = KtB::P;  // 960 interface slots (the 16 x 4 x 4 brick has as many)
-static_assert(KtBrick<16, 4, 4>::P == kKtP, "both bricks use the same LDS segment sizes");
+constexpr int kKtP = KtB::P;  // 960 interface slots (the 8 x 8 x 4 brick has as many)
+static_assert(KtBrick<8, 8, 4>::P == kKtP, "both bricks use the same LDS segment sizes");
 
 // Smaller-magnitude argument when both have the same strict sign, else 0.
 __device__ __forceinline__ double minmod(double a, double b) {
@@ -126,7 +129,7 @@ __device__ __forceinline__ void kt_interface(const double* U, size_t fs, const D
   for (int q = 0; q < 4; ++q) fh[q] = 0.5 * (FL[q] + FR[q]) - 0.5 * c * (qR[q] - qL[q]);
 }
 
-// Brick b of the 8 x 8 x 4 decomposition for workgroup v. Consecutive workgroups
+// Brick b of the decomposition for workgroup v. Consecutive workgroups
 // go round-robin to the 8 XCDs, so workgroups v % 8 == q share XCD q's L2. Where the
 // brick grid allows, XCD q owns the q-th slab of brick layers along z and walks it in
 // columns of 4 x 4 bricks, z fastest: the bricks resident together on an XCD (about
@@ -199,12 +202,12 @@ __device__ __forceinline__ void kt_brick_divergence(const double* U, size_t fs, 
   __syncthreads();  // fh may be refilled for another brick
 }
 
-// Workgroups of k_fluid_kt: one per 8 x 8 x 4 brick (partial bricks at the upper faces).
+// Workgroups of k_fluid_kt: one per brick (partial bricks at the upper faces).
 inline unsigned kt_bricks(const DevParams& P) {
   return (unsigned)(((P.n[0] + kKtBX - 1) / kKtBX) * ((P.n[1] + kKtBY - 1) / kKtBY) * ((P.n[2] + kKtBZ - 1) / kKtBZ));
 }
 
-// The Kurganov-Tadmor divergence of one grid, one 8 x 8 x 4 brick per workgroup.
+// The Kurganov-Tadmor divergence of one grid, one brick per workgroup.
 __global__ __launch_bounds__(kKtThreads) void k_fluid_kt(const double* U, size_t fs, DevParams P, double* D) {
   __shared__ double fh[4][kKtP];
   const int nbx = (P.n[0] + kKtBX - 1) / kKtBX, nby = (P.n[1] + kKtBY - 1) / kKtBY;
