@@ -212,13 +212,6 @@ __device__ __forceinline__ void lds_derivs(const double* c, const DevParams& P, 
   }
 }
 
-__device__ __forceinline__ int wrap_halo(int x, int n) {
-  x = x < 0 ? x + n : x;
-  x = x >= n ? x - n : x;
-  return x >= n ? x - n : x;
-}
-
-
 // Halo box for staging by LDS-direct loads: x runs from i0 - 4 to i0 + BX + 3 (BX + 8 points,
 // one more on each side than the stencils need), so that with n0 even every aligned pair of
 // x-neighbours (2m, 2m + 1) of the box is two consecutive doubles in memory, 16-byte aligned,
@@ -251,12 +244,7 @@ __device__ __forceinline__ void wait_vm(int n) {
   switch (n) {  // the count is an instruction immediate
     case 0: __builtin_amdgcn_s_waitcnt(0x0F70); break;
     case 5: __builtin_amdgcn_s_waitcnt(0x0F75); break;
-    case 6: __builtin_amdgcn_s_waitcnt(0x0F76); break;
     case 10: __builtin_amdgcn_s_waitcnt(0x0F7A); break;
-    case 12: __builtin_amdgcn_s_waitcnt(0x0F7C); break;
-    case 15: __builtin_amdgcn_s_waitcnt(0x0F7F); break;
-    case 18: __builtin_amdgcn_s_waitcnt(0x4F72); break;
-    case 25: __builtin_amdgcn_s_waitcnt(0x4F79); break;
     default: __builtin_amdgcn_s_waitcnt(0x0F70); break;  // any other count: wait for everything
   }
 }
