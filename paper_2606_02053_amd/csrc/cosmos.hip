@@ -23,6 +23,7 @@
 #include "scalar_device.hpp"
 #include "scalar_lds.hpp"
 #include "adjoint_point.hpp"
+#include "gather_boxes.hpp"
 
 using namespace cosmos;
 
