@@ -286,8 +286,8 @@ int cosmos_constraints_noalloc(const cosmos_grid* grid, const cosmos_params* par
                                double* norms_dev, double* H_out, double* M_out, void* stream);
 
 /* Bytes of device workspace for cosmos_rhs_vjp / cosmos_adjoint_step: status counters, the
- * recomputed stage states U2..U4 and one more state-sized array, two state-sized cotangent buffers and
- * 136 * N3 doubles of per-point cotangent scratch. 0 for an invalid grid. */
+ * recomputed stage states U2..U4, two state-sized cotangent buffers and 136 * N3 doubles of per-point
+ * cotangent scratch. 0 for an invalid grid. */
 size_t cosmos_adjoint_workspace_bytes(const cosmos_grid* grid);
 
 /* Transposed Jacobian of the discrete right-hand side at state u and time t applied to kbar:

@@ -96,6 +96,15 @@ def test_grid_size_limits(C):
     assert C.cosmos_adjoint_workspace_bytes(C.make_grid((2048, 2048, 128), 1.0)) == 0
 
 
+def test_adjoint_workspace_holds_its_arrays_and_nothing_else(C):
+    """Status counters, U2..U4, two cotangent states and 136 scratch arrays, each 256-byte aligned."""
+    for n in ((16, 16, 16), (21, 8, 9), (96, 96, 96)):
+        up = lambda b: (b + 255) // 256 * 256
+        N3 = n[0] * n[1] * n[2]
+        want = 256 + 5 * up(25 * N3 * 8) + up(136 * N3 * 8)
+        assert C.cosmos_adjoint_workspace_bytes(C.make_grid(n, 1.0)) == want
+
+
 def test_stage_keeping_entry_points_validate_on_host(C):
     g = C.make_grid(16, 4.0)
     p = C.make_params()
