@@ -63,17 +63,17 @@ import torch
 METRIC = "grid-point RK4 updates/sec FP64 at 256^3 (+ batched runs/sec, adjoint cost)"
 HBM_PEAK_GBS = 8000.0
 FP64_PEAK_TFLOPS = 78.6
-# algorithmic HBM bytes per point per RK4 step: 16 passes over the 25 FP64 fields
-# (stage 1 reads u, writes acc and U2; stages 2-3 read U_s, u, acc and write acc, U_{s+1};
-#  stage 4 reads U4, acc and writes u): 16 * 25 * 8
-BYTES_PER_POINT_STEP = 3200.0
+# algorithmic HBM bytes per point per RK4 step: 12 passes over the 25 FP64 fields
+# (stage 1 reads u, writes U2; stage 2 reads U2, u, writes the carried S = U2 - u + 2 U3 and U3;
+#  stage 3 reads U3, u, writes U4; stage 4 reads U4, S, writes u): 12 * 25 * 8
+BYTES_PER_POINT_STEP = 2400.0
 LAUNCHES_PER_STEP = 4
-# with the scalar field, per point and RK4 step: the plain 3200 B; the scalar stage reads 12
+# with the scalar field, per point and RK4 step: the plain 2400 B; the scalar stage reads 12
 # geometry fields (chi, gt_ij, K, alpha, beta^i) and (phi, Pi) in every stage (112 B), acc and u_n
 # of (phi, Pi) as its mode needs (0 / 32 / 32 / 16 B), and writes the 11 source arrays and the
 # field's acc and next state (120 / 120 / 120 / 104 B): 992 B; the stage kernel reads 10 source
 # arrays per stage (320 B)
-SCALAR_BYTES_PER_POINT_STEP = 3200.0 + 992.0 + 320.0
+SCALAR_BYTES_PER_POINT_STEP = BYTES_PER_POINT_STEP + 992.0 + 320.0
 
 
 def step_roofline(point_updates_per_s, bytes_per_point_step, kernels):

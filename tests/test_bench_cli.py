@@ -39,3 +39,12 @@ def test_source_hash_gates_the_committed_counters(tmp_path, monkeypatch):
     f.write_text(body.format(h="0" * 16))
     assert bench.measured_traffic("lds:16x4x4:blocked", 4096) is None  # counters of other sources
     assert bench.measured_counters("lds:16x4x4:blocked", 4096) == (None, None)
+
+
+def test_algorithmic_bytes_are_those_the_stages_move():
+    """The HBM roofline prices a step at the state arrays the four stages read and write: u and U2; U2, u, S
+    and U3; U3, u and U4; U4, S and the new u. The scalar field adds its own stage and the sources."""
+    sys.path.insert(0, ROOT)
+    import bench
+    assert bench.BYTES_PER_POINT_STEP == (2 + 4 + 3 + 3) * 25 * 8
+    assert bench.SCALAR_BYTES_PER_POINT_STEP == bench.BYTES_PER_POINT_STEP + 992 + 320
