@@ -11,10 +11,10 @@
 // One pre-pass kernel per stage forms the whole flux divergence: a workgroup owns
 // a 16 x 4 x 4 brick, evaluates every interface flux of the brick once into LDS
 // (17x4x4 + 16x5x4 + 16x4x5 = 912 interfaces for 256 points, in three wave-aligned
-// segments of 320) and differences them. About half of its time is arithmetic, half
-// the L1's work on 34 loads an interface, whose rows of 16 points are whole cache
-// lines (an 8 x 8 x 4 brick, with 896 interfaces, has twice as many rows): 96^3 99.9 ->
-// 95.6 us, 128^3 235 -> 220 us, 50x41x37 22.6 -> 19.6 us.
+// segments of 320) and differences them. Arithmetic issues in two thirds of the cycles,
+// and the L1 serves accesses in two thirds of them, for 34 loads an interface whose
+// rows of 16 points are whole cache lines (an 8 x 8 x 4 brick, with 896 interfaces, has twice as many rows): 96^3 99.9 ->
+// 95.6 us, 128^3 235 -> 220 us, 50x41x37 22.6 -> 19.6 us, 64^3 27.1 -> 27.6 us.
 // The stage kernel then reads the divergence at the point itself.
 #pragma once
 #include "bssn_device.hpp"
